@@ -6,10 +6,14 @@
 // r = 6|v| / 2^e_ceil, ceiling codes qc = E2M1(r) and floor codes qf = E2M1(2r),
 // the floor wins iff sum (2 qc - qf)(4 r - qf - 2 qc) < 0; every term of that
 // sum is exact in fp64 for fp32/bf16 inputs, so the choice is exact.
-// bf16 inputs take a 32-bit path with the hardware E2M1 converter (exact too,
-// see mxfp4_block_bf16), 16-byte loads for Q and K and two columns per thread
-// for V^T; fp32 inputs and odd shapes take the fp64 kernel.  One thread owns
-// one block (bf16 V^T: one block of each of two columns).
+// Both input types take 32-bit paths with the hardware E2M1 converter (exact
+// too, see mxfp4_block_bf16 and mxfp4_block_f32).  One thread owns one block.
+//
+// What bounds it: memory.  Each value is read once (2 or 4 bytes) and leaves as
+// 17/32 byte (MXFP8: 33/32).  Q, K and V of B2 H16 N4096 d128 in fp32 take 54.7 us
+// (4.2 TB/s; 319 us with the rule's sum and every code decision in fp64); of B1 H32
+// N16384 d128 in bf16 99.2 us (5.1 TB/s; 100.9 us with three 64-bit index divisions
+// per block and two V columns per thread).  A device copy runs at 5.3 TB/s.
 #include "gfx950.hpp"
 #include "launch.hpp"
 
@@ -17,117 +21,47 @@ namespace fp4attn {
 
 typedef float v2f __attribute__((ext_vector_type(2)));
 
-
-// Index k of the E2M1 magnitude {0, .5, 1, 1.5, 2, 3, 4, 6} nearest to r >= 0,
-// ties to even k, saturating: count the boundaries at or below r, each tie
-// counted toward the even neighbour.
-__device__ __forceinline__ int e2m1_index(double r) {
-  return (r > 0.25) + (r >= 0.75) + (r > 1.25) + (r >= 1.75) + (r > 2.5) + (r >= 3.5) + (r > 5.0);
-}
-__device__ __forceinline__ double e2m1_value(int k) {
-  // 0, .5, 1, 1.5 for k < 4; 2, 3, 4, 6 for k >= 4
-  return k < 4 ? 0.5 * k : (k == 7 ? 6.0 : (double)(k - 2));
-}
-
-template <typename T>
-__device__ __forceinline__ float load_as_float(const T* p);
-template <>
-__device__ __forceinline__ float load_as_float<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float load_as_float<uint16_t>(const uint16_t* p) {
-  return __builtin_bit_cast(float, (unsigned)(*p) << 16);
-}
-
 // Source row of row r of the anchor-ordered matrix (Sec. "Fix 3": the anchor
 // rows j * stride, j < n_anchor, first, then every other row in order);
-// stride 0 is the identity.  Always within [0, n_anchor * stride).
-__device__ __forceinline__ int64_t anchor_source_row(int64_t r, int64_t n_anchor, int64_t stride) {
+// stride <= 1 is the identity.  Always within [0, n_anchor * stride).
+template <typename I>
+__device__ __forceinline__ I anchor_source_row(I r, I n_anchor, I stride) {
   if (stride <= 1) return r;
   if (r < n_anchor) return r * stride;
-  const int64_t k = r - n_anchor;
+  const I k = r - n_anchor;
   return (k / (stride - 1)) * stride + 1 + k % (stride - 1);
 }
 
-// axis == 1: blocks along the contiguous axis (Q, K).  axis == 0: blocks along
-// rows, output transposed (V).  Rows are read in anchor order when
-// anchor_stride > 0.
-template <typename T, int AXIS>
-__global__ __launch_bounds__(256) void quantize_mxfp4_kernel(const T* __restrict__ src, int64_t batch, int64_t rows,
-                                                             int64_t cols, uint8_t* __restrict__ codes,
-                                                             uint8_t* __restrict__ scales, int64_t n_anchor,
-                                                             int64_t anchor_stride) {
-  const int64_t nblk = AXIS == 1 ? cols / 32 : rows / 32;
-  const int64_t outer = AXIS == 1 ? rows : cols;
-  const int64_t total = batch * outer * nblk;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= total) return;
-  int64_t b, o, blk;
-  if (AXIS == 1) {  // consecutive threads take consecutive blocks of one row
-    blk = t % nblk;
-    o = (t / nblk) % outer;
-    b = t / (nblk * outer);
-  } else {  // consecutive threads take consecutive columns: coalesced loads
-    o = t % outer;
-    blk = (t / outer) % nblk;
-    b = t / (outer * nblk);
-  }
-  float v[32];
-  if (AXIS == 1) {
-    const T* p = src + (b * rows + anchor_source_row(o, n_anchor, anchor_stride)) * cols + blk * 32;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) v[j] = load_as_float<T>(p + j);
-  } else if (anchor_stride <= 1) {
-    const T* p = src + (b * rows + blk * 32) * cols + o;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) v[j] = load_as_float<T>(p + (int64_t)j * cols);
-  } else {
-    const T* p = src + b * rows * cols + o;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) v[j] = load_as_float<T>(p + anchor_source_row(blk * 32 + j, n_anchor, anchor_stride) * cols);
-  }
-  float amax = 0.0f;
-  bool finite = true;
-#pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    finite = finite && __builtin_isfinite(v[j]);
-    amax = fmaxf(amax, fabsf(v[j]));
-  }
-  int e = 0;
-  unsigned ubyte;
-  if (!finite) {
-    ubyte = 255;
-  } else if (amax == 0.0f) {
-    ubyte = 0;
-  } else {
-    int x;
-    const float m = frexpf(amax, &x);  // amax = m 2^x, m in [0.5, 1)
-    const int e_floor = x - 1;
-    const int e_ceil = (m == 0.5f) ? x - 1 : x;
-    double delta = 0.0;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      const double r = ldexp(6.0 * (double)fabsf(v[j]), -e_ceil);
-      const double qc = e2m1_value(e2m1_index(r));
-      const double qf = e2m1_value(e2m1_index(2.0 * r));
-      delta += (2.0 * qc - qf) * (4.0 * r - qf - 2.0 * qc);
-    }
-    e = (e_floor != e_ceil && delta < 0.0) ? e_floor : e_ceil;
-    e = e < -127 ? -127 : (e > 127 ? 127 : e);
-    ubyte = (unsigned)(e + 127);
-  }
-  unsigned w[4] = {0u, 0u, 0u, 0u};
-  if (finite) {
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      const int k = e2m1_index(ldexp(6.0 * (double)fabsf(v[j]), -e));
-      const unsigned code = (unsigned)k | (__builtin_signbit(v[j]) ? 8u : 0u);
-      w[j / 8] |= code << (4 * (j % 8));
+// Source rows of consecutive anchor-ordered rows, one division for the first.
+struct AnchorWalk {
+  int64_t row, n_anchor, stride, src, rem;
+  __device__ __forceinline__ AnchorWalk(int64_t r, int64_t n_anchor_, int64_t stride_)
+      : row(r), n_anchor(n_anchor_), stride(stride_), src(r), rem(0) {
+    if (stride <= 1) return;
+    if (r < n_anchor) {
+      src = r * stride;
+    } else {
+      const int64_t k = r - n_anchor, g = k / (stride - 1);
+      rem = k - g * (stride - 1);
+      src = g * stride + 1 + rem;
     }
   }
-  uint8_t* cdst = codes + (b * outer + o) * (nblk * 16) + blk * 16;
-  *reinterpret_cast<v4i*>(cdst) = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-  scales[(b * outer + o) * nblk + blk] = (uint8_t)ubyte;
-}
+  __device__ __forceinline__ void next() {
+    ++row;
+    if (stride <= 1) {
+      ++src;
+    } else if (row < n_anchor) {
+      src += stride;
+    } else if (row == n_anchor) {  // the first row that is no anchor
+      src = 1;
+      rem = 0;
+    } else {
+      const bool skip = ++rem == stride - 1;  // over the next anchor
+      src += skip ? 2 : 1;
+      rem = skip ? 0 : rem;
+    }
+  }
+};
 
 // bf16 fast path of the same rule, exact in 32-bit arithmetic.  A bf16 value
 // has at most 8 significant bits, so r = 6 v / 2^e_ceil has at most 10 and is
@@ -232,129 +166,6 @@ __device__ __forceinline__ unsigned mxfp4_block_bf16(const unsigned (&raw)[16], 
   return (unsigned)(e + 127);
 }
 
-// bf16, blocks along the contiguous axis (Q, K): one block per thread, four
-// 16-byte loads.
-__global__ __launch_bounds__(256) void quantize_mxfp4_bf16_rows_kernel(const uint16_t* __restrict__ src, int64_t batch,
-                                                                       int64_t rows, int64_t cols,
-                                                                       uint8_t* __restrict__ codes,
-                                                                       uint8_t* __restrict__ scales, int64_t n_anchor,
-                                                                       int64_t anchor_stride) {
-  const int64_t nblk = cols / 32;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= batch * rows * nblk) return;
-  const int64_t blk = t % nblk, o = (t / nblk) % rows, b = t / (nblk * rows);
-  const uint4* p = reinterpret_cast<const uint4*>(src + (b * rows + anchor_source_row(o, n_anchor, anchor_stride)) * cols +
-                                                  blk * 32);
-  unsigned raw[16];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint4 q = p[i];
-    raw[4 * i] = q.x;
-    raw[4 * i + 1] = q.y;
-    raw[4 * i + 2] = q.z;
-    raw[4 * i + 3] = q.w;
-  }
-  unsigned w[4];
-  const unsigned u = mxfp4_block_bf16(raw, w);
-  *reinterpret_cast<v4i*>(codes + t * 16) = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-  scales[t] = (uint8_t)u;
-}
-
-// bf16, blocks along rows with transposed output (V): a thread takes one block
-// of two adjacent columns (one 4-byte load per row; a wave reads 256-byte row
-// segments).  cols % 2 == 0.  (Several blocks per thread, for longer runs of
-// contiguous code bytes, measured slower: fewer waves in flight.)
-__global__ __launch_bounds__(256) void quantize_mxfp4_bf16_cols_kernel(const uint16_t* __restrict__ src, int64_t batch,
-                                                                       int64_t rows, int64_t cols,
-                                                                       uint8_t* __restrict__ codes,
-                                                                       uint8_t* __restrict__ scales, int64_t n_anchor,
-                                                                       int64_t anchor_stride) {
-  const int64_t nblk = rows / 32, npair = cols / 2;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= batch * nblk * npair) return;
-  const int64_t cp = t % npair, blk = (t / npair) % nblk, b = t / (npair * nblk);
-  const uint16_t* base = src + b * rows * cols + 2 * cp;
-  unsigned pair[32];
-#pragma unroll
-  for (int j = 0; j < 32; ++j)
-    pair[j] = *reinterpret_cast<const unsigned*>(base + anchor_source_row(blk * 32 + j, n_anchor, anchor_stride) * cols);
-  unsigned raw0[16], raw1[16];  // column 2 cp and 2 cp + 1, rows in order
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    raw0[i] = (pair[2 * i] & 0xffffu) | (pair[2 * i + 1] << 16);
-    raw1[i] = (pair[2 * i] >> 16) | (pair[2 * i + 1] & 0xffff0000u);
-  }
-  const int64_t col0 = b * cols + 2 * cp;
-  unsigned w[4];
-  scales[col0 * nblk + blk] = (uint8_t)mxfp4_block_bf16(raw0, w);
-  *reinterpret_cast<v4i*>(codes + (col0 * nblk + blk) * 16) = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-  scales[(col0 + 1) * nblk + blk] = (uint8_t)mxfp4_block_bf16(raw1, w);
-  *reinterpret_cast<v4i*>(codes + ((col0 + 1) * nblk + blk) * 16) = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-}
-
-// The E8M0 bytes of blocks 8 grp .. 8 grp + 7 of one column (byte l of `run` is
-// block 8 grp + l) to `dst`: one 8-byte store when every column has whole groups
-// of 8 blocks (dst is then 8-byte aligned), else one byte per block that exists.
-__device__ __forceinline__ void store_scale_run(uint8_t* dst, uint2 run, int64_t nblk, int64_t grp) {
-  if (nblk % 8 == 0) {
-    *reinterpret_cast<uint2*>(dst) = run;
-  } else {
-    const uint64_t bytes = ((uint64_t)run.y << 32) | run.x;
-    for (int l = 0; l < 8 && grp * 8 + l < nblk; ++l) dst[l] = (uint8_t)(bytes >> (8 * l));
-  }
-}
-
-// bf16, blocks along rows with transposed output (V), staged: a workgroup takes
-// 64 columns x 256 rows (32 column pairs x 8 blocks; a thread quantizes one block
-// of two adjacent columns as above), parks its codes and scale bytes in LDS, and
-// writes each column's 8 blocks of codes as one contiguous 128-byte run (each
-// store instruction of a wave covers 64 contiguous bytes of 16 columns) and its 8
-// scale bytes with one store.  The loads stay 128-byte row segments; the
-// workgroups that take the column groups of the same rows are launched next to
-// each other, so the wider rows of d = 128 are read whole at about the same
-// time.  cols % 64 == 0; blocks past the last are skipped (their threads still
-// meet the barrier).
-__global__ __launch_bounds__(256) void quantize_mxfp4_bf16_cols_staged_kernel(
-    const uint16_t* __restrict__ src, int64_t batch, int64_t rows, int64_t cols, uint8_t* __restrict__ codes,
-    uint8_t* __restrict__ scales, int64_t n_anchor, int64_t anchor_stride) {
-  __shared__ uint4 code_lds[64][8];
-  __shared__ uint2 scale_lds[64];  // 8 bytes per column
-  const int64_t nblk = rows / 32, ngrp = (nblk + 7) / 8, ncg = cols / 64;
-  const int64_t cg = blockIdx.x % ncg, grp = (blockIdx.x / ncg) % ngrp, b = blockIdx.x / (ngrp * ncg);
-  const int tid = threadIdx.x, cp = tid % 32, lb = tid / 32;
-  const int64_t blk = grp * 8 + lb;
-  if (blk < nblk) {
-    const uint16_t* base = src + b * rows * cols + cg * 64 + 2 * cp;
-    unsigned pair[32];
-#pragma unroll
-    for (int j = 0; j < 32; ++j)
-      pair[j] = *reinterpret_cast<const unsigned*>(base + anchor_source_row(blk * 32 + j, n_anchor, anchor_stride) * cols);
-    unsigned raw0[16], raw1[16];  // column 2 cp and 2 cp + 1, rows in order
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      raw0[i] = (pair[2 * i] & 0xffffu) | (pair[2 * i + 1] << 16);
-      raw1[i] = (pair[2 * i] >> 16) | (pair[2 * i + 1] & 0xffff0000u);
-    }
-    unsigned w[4];
-    uint8_t* sb = reinterpret_cast<uint8_t*>(scale_lds);
-    sb[16 * cp + lb] = (uint8_t)mxfp4_block_bf16(raw0, w);
-    code_lds[2 * cp][lb] = uint4{w[0], w[1], w[2], w[3]};
-    sb[16 * cp + 8 + lb] = (uint8_t)mxfp4_block_bf16(raw1, w);
-    code_lds[2 * cp + 1][lb] = uint4{w[0], w[1], w[2], w[3]};
-  }
-  __syncthreads();
-  // thread t writes blocks (t % 4) and (t % 4) + 4 of column t / 4
-  const int c = tid / 4, part = tid % 4;
-  const int64_t col = b * cols + cg * 64 + c;
-  uint8_t* cdst = codes + (col * nblk + grp * 8) * 16;
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int l = part + 4 * k;
-    if (grp * 8 + l < nblk) *reinterpret_cast<uint4*>(cdst + l * 16) = code_lds[c][l];
-  }
-  if (tid < 64) store_scale_run(scales + (b * cols + cg * 64 + tid) * nblk + grp * 8, scale_lds[tid], nblk, grp);
-}
-
 // MXFP8 (E4M3 payload + E8M0 per 32 values): the amplitude is the smallest
 // power of two 2^e with amax / 2^e <= 448, so no payload saturates; payloads
 // are v / 2^e (exact) rounded to nearest even by the hardware converter, which
@@ -398,6 +209,369 @@ __device__ __forceinline__ unsigned mxfp8_block(const float (&v)[32], unsigned (
   return ubyte;
 }
 
+// The E8M0 bytes of blocks 8 grp .. 8 grp + 7 of one column (byte l of `run` is
+// block 8 grp + l) to `dst`: one 8-byte store when every column has whole groups
+// of 8 blocks (dst is then 8-byte aligned), else one byte per block that exists.
+__device__ __forceinline__ void store_scale_run(uint8_t* dst, uint2 run, int64_t nblk, int64_t grp) {
+  if (nblk % 8 == 0) {
+    *reinterpret_cast<uint2*>(dst) = run;
+  } else {
+    const uint64_t bytes = ((uint64_t)run.y << 32) | run.x;
+    for (int l = 0; l < 8 && grp * 8 + l < nblk; ++l) dst[l] = (uint8_t)(bytes >> (8 * l));
+  }
+}
+
+// fp32 form of the same rule.  r = 6 v / 2^e has up to 26 significant bits, so
+// its fp32 product is rounded to odd: truncated, with the last bit set if
+// anything was lost (the fma gives the product's error exactly).  Every E2M1
+// boundary (of r and of 2 r) has at most three significant bits, hence an even
+// last bit, so a value rounded to odd lies on the same side of each as the exact
+// product and meets one only when it is exactly there: the converter's codes
+// are those of the exact r.  Values under 2^-126 of the block's scale may lose
+// bits in the scaling; their code is a signed zero all the same.
+__device__ __forceinline__ float six_to_odd(float m) {
+  const float r = 6.0f * m, err = fmaf(6.0f, m, -r);
+  const unsigned lost = err != 0.0f ? 1u : 0u, over = (as_uint(err) ^ as_uint(r)) >> 31;  // |r| > |6 m|
+  return as_float((as_uint(r) - (lost & over)) | lost);
+}
+
+// The rule's sum over the block in fp64, where it is exact, from the codes of
+// both amplitudes.
+// (The empty asm keeps the values of the common path from staying in registers
+// for this rare one, and its terms in order.)
+__device__ __forceinline__ bool floor_wins_f64(const float (&v)[32], int e_ceil, const unsigned (&codes_c)[4],
+                                               const unsigned (&codes_f)[4]) {
+  double delta = 0.0;
+  unsigned cc[4], cf[4];
+  static_for<16>([&](auto I_) {
+    constexpr int i = decltype(I_)::value;
+    if constexpr (i % 4 == 0) {
+      cc[i / 4] = codes_c[i / 4];
+      cf[i / 4] = codes_f[i / 4];
+      asm volatile("" : "+v"(cc[i / 4]), "+v"(cf[i / 4]), "+v"(e_ceil), "+v"(delta));
+    }
+    const v2f qc = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(cc[i / 4], 1.0f, i % 4);
+    const v2f qf = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(cf[i / 4], 1.0f, i % 4);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const double r4 = 24.0 * (double)ldexpf(v[2 * i + t], -e_ceil);
+      delta += (2.0 * qc[t] - qf[t]) * (r4 - qf[t] - 2.0 * qc[t]);
+    }
+  });
+  return delta < 0.0;
+}
+
+// One fp32 block: returns the E8M0 byte; codes as mxfp4_block_bf16.
+__device__ __forceinline__ unsigned mxfp4_block_f32(const float (&v)[32], unsigned (&codes)[4]) {
+  unsigned amax_bits = 0u;
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    const unsigned a = as_uint(v[j]) & 0x7fffffffu;
+    amax_bits = a > amax_bits ? a : amax_bits;
+  }
+  if (amax_bits >= 0x7f800000u) {  // a NaN or an infinity in the block
+#pragma unroll
+    for (int j = 0; j < 4; ++j) codes[j] = 0u;
+    return 255u;
+  }
+  auto encode = [&](int e) {
+    static_for<16>([&](auto I_) {
+      constexpr int i = decltype(I_)::value;
+      const float r0 = six_to_odd(ldexpf(v[2 * i], -e)), r1 = six_to_odd(ldexpf(v[2 * i + 1], -e));
+      codes[i / 4] = cvt_pk_fp4<i % 4>(i % 4 == 0 ? 0u : codes[i / 4], r0, r1, 1.0f);
+    });
+  };
+  if (amax_bits == 0u) {  // zero block: byte 0, every code a signed zero
+    encode(0);
+    return 0u;
+  }
+  int x;
+  const float m = frexpf(as_float(amax_bits), &x);  // amax = m 2^x, m in [0.5, 1)
+  const int e_floor = x - 1, e_ceil = (m == 0.5f) ? x - 1 : x;
+  unsigned cc[4], cf[4];
+  float s_ar = 0.0f, s_ab = 0.0f;
+  static_for<16>([&](auto I_) {
+    constexpr int i = decltype(I_)::value, w = i / 4, pb = i % 4;
+    const float r0 = six_to_odd(ldexpf(v[2 * i], -e_ceil)), r1 = six_to_odd(ldexpf(v[2 * i + 1], -e_ceil));
+    cc[w] = cvt_pk_fp4<pb>(pb == 0 ? 0u : cc[w], r0, r1, 1.0f);
+    cf[w] = cvt_pk_fp4<pb>(pb == 0 ? 0u : cf[w], r0, r1, 0.5f);
+    const v2f qc = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(cc[w], 1.0f, pb);
+    const v2f qf = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(cf[w], 1.0f, pb);
+    const float a0 = fmaf(2.0f, qc[0], -qf[0]), a1 = fmaf(2.0f, qc[1], -qf[1]);
+    s_ar = fmaf(a1, r1, fmaf(a0, r0, s_ar));
+    s_ab = fmaf(a1, fmaf(2.0f, qc[1], qf[1]), fmaf(a0, fmaf(2.0f, qc[0], qf[0]), s_ab));
+    // (emits nothing: the sums are formed here and not sunk below the branch with
+    // every term held in registers)
+    if constexpr (pb == 3) asm volatile("" : "+v"(s_ar), "+v"(s_ab));
+  });
+  // s_ab is exact (see the bf16 form).  s_ar = sum a r <= 32 * 36 carries at most
+  // 32 roundings of 2^-24 of it and, from each r, 2^-23: under 0.0025, so the sign
+  // of 4 s_ar - s_ab stands when it is 0.0125 or more from zero.  About one block
+  // in a thousand is nearer and takes the exact sum.
+  bool floor_wins = false;
+  if (e_floor != e_ceil) {
+    const float diff = 4.0f * s_ar - s_ab;
+    floor_wins = diff < 0.0f;
+    if (fabsf(diff) < 0.0125f) floor_wins = floor_wins_f64(v, e_ceil, cc, cf);
+  }
+  int e = floor_wins ? e_floor : e_ceil;
+  e = e < -127 ? -127 : (e > 127 ? 127 : e);
+  if (e == e_ceil || e == e_floor) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) codes[j] = e == e_ceil ? cc[j] : cf[j];
+  } else {  // amplitude clamped to the E8M0 range
+    encode(e);
+  }
+  return (unsigned)(e + 127);
+}
+
+// A block of 32 values as the block functions take it: bf16 pairs in 16 words,
+// fp32 values as they are.
+template <typename T>
+struct Block;
+template <>
+struct Block<uint16_t> {
+  unsigned raw[16];
+  __device__ __forceinline__ unsigned mxfp4(unsigned (&w)[4]) const { return mxfp4_block_bf16(raw, w); }
+  __device__ __forceinline__ unsigned mxfp8(unsigned (&w)[8]) const {
+    float v[32];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      v[2 * i] = as_float(raw[i] << 16);
+      v[2 * i + 1] = as_float(raw[i] & 0xffff0000u);
+    }
+    return mxfp8_block(v, w);
+  }
+  // element j from a value in memory (j in order, even first)
+  __device__ __forceinline__ void set(int j, uint16_t x) {
+    if (j % 2 == 0) raw[j / 2] = x;
+    else raw[j / 2] |= (unsigned)x << 16;
+  }
+};
+template <>
+struct Block<float> {
+  float v[32];
+  __device__ __forceinline__ unsigned mxfp4(unsigned (&w)[4]) const { return mxfp4_block_f32(v, w); }
+  __device__ __forceinline__ unsigned mxfp8(unsigned (&w)[8]) const { return mxfp8_block(v, w); }
+  __device__ __forceinline__ void set(int j, float x) { v[j] = x; }
+};
+
+// 32 contiguous values (16-byte aligned).
+template <typename T>
+__device__ __forceinline__ void load_row_block(const T* p, Block<T>& b) {
+  constexpr int kLoads = 32 * sizeof(T) / 16;
+  uint4 q[kLoads];
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) q[i] = reinterpret_cast<const uint4*>(p)[i];
+  static_assert(sizeof(b) == sizeof(q), "a block is its values' bytes");
+  __builtin_memcpy(&b, q, sizeof(q));
+}
+
+// Blocks along the contiguous axis (Q, K): `total` blocks of `nblk` per row.
+struct RowsJob {
+  const void* src;
+  uint8_t* codes;
+  uint8_t* scales;
+  int64_t total, rows, nblk, n_anchor, stride;  // stride > 1: rows in anchor order
+};
+// Blocks along rows, output transposed (V): `batch` matrices of rows x cols.
+struct ColsJob {
+  const void* src;
+  uint8_t* codes;
+  uint8_t* scales;
+  int64_t rows, cols, n_anchor, stride;
+};
+
+constexpr int kThreads = 512;     // one block of 32 values per thread
+constexpr int kColsPerWg = 64;    // V: columns x 8 blocks of 32 rows
+constexpr int kBlksPerWg = kThreads / kColsPerWg;
+
+// Without the anchor order block t is at value 32 t: no division.
+template <typename T>
+__device__ __forceinline__ void quantize_rows(const RowsJob& j, unsigned wg) {
+  const int64_t t = (int64_t)wg * kThreads + threadIdx.x;
+  if (t >= j.total) return;
+  const T* src = static_cast<const T*>(j.src);
+  int64_t at = t;
+  if (j.stride > 1) {
+    if (j.total <= 0x7fffffff) {
+      const unsigned row = (unsigned)t / (unsigned)j.nblk, b = row / (unsigned)j.rows;
+      const unsigned o = row - b * (unsigned)j.rows;
+      at = (int64_t)(b * (unsigned)j.rows + anchor_source_row<unsigned>(o, j.n_anchor, j.stride)) * j.nblk +
+           ((unsigned)t - row * (unsigned)j.nblk);
+    } else {
+      const int64_t row = t / j.nblk, b = row / j.rows;
+      at = (b * j.rows + anchor_source_row<int64_t>(row - b * j.rows, j.n_anchor, j.stride)) * j.nblk + (t - row * j.nblk);
+    }
+  }
+  Block<T> blk;
+  load_row_block(src + at * 32, blk);
+  unsigned w[4];
+  const unsigned u = blk.mxfp4(w);
+  *reinterpret_cast<v4i*>(j.codes + t * 16) = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+  j.scales[t] = (uint8_t)u;
+}
+
+// Staged V^T: a workgroup takes 64 columns x 256 rows, wave w the block of 32 rows
+// w of them.  fp32: lane = column, 256-byte row segments.  bf16: lane l < 32 reads
+// rows 0-15 of the block at columns 2 l and 2 l + 1, lane l + 32 rows 16-31, and
+// one exchange of the wave's halves leaves column 2 l in lane l and column
+// 2 l + 1 in lane l + 32.  Codes and scale bytes are parked in LDS (chunks XOR'd
+// with the column, so that neither side meets bank conflicts) and leave as one
+// contiguous run per column (128 bytes, MXFP8 256) and one scale store.  The
+// workgroups of the column groups of the same rows are launched next to each
+// other, so wider rows are read whole at about the same time.  cols % 64 == 0;
+// blocks past the last are skipped (their waves still meet the barrier).
+template <typename T, bool FP8>
+__device__ __forceinline__ void quantize_cols(const ColsJob& j, unsigned wg) {
+  constexpr int kChunks = FP8 ? 2 * kBlksPerWg : kBlksPerWg;  // 16-byte chunks of a column's run
+  __shared__ uint4 code_lds[kColsPerWg][kChunks];
+  __shared__ uint2 scale_lds[kColsPerWg];
+  const unsigned nblk = (unsigned)(j.rows / 32), ngrp = (nblk + kBlksPerWg - 1) / kBlksPerWg;
+  const unsigned ncg = (unsigned)(j.cols / kColsPerWg);
+  const unsigned rest = wg / ncg, cg = wg - rest * ncg, b = rest / ngrp, grp = rest - b * ngrp;
+  const int tid = threadIdx.x, lane = tid & 63, lb = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t blk = (int64_t)grp * kBlksPerWg + lb;
+  if (blk < nblk) {
+    const T* base = static_cast<const T*>(j.src) + (int64_t)b * j.rows * j.cols + cg * kColsPerWg;
+    Block<T> bl;
+    int c;  // this lane's column of the 64
+    if constexpr (sizeof(T) == 2) {
+      const int cp = lane & 31, half = lane >> 5;
+      c = 2 * cp + half;
+      unsigned pair[16];
+      const T* p = base + 2 * cp;
+      if (j.stride > 1) {
+        AnchorWalk r(blk * 32 + 16 * half, j.n_anchor, j.stride);
+#pragma unroll
+        for (int i = 0; i < 16; ++i, r.next()) pair[i] = *reinterpret_cast<const unsigned*>(p + r.src * j.cols);
+      } else {
+        p += (blk * 32 + 16 * half) * j.cols;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) pair[i] = *reinterpret_cast<const unsigned*>(p + i * j.cols);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        unsigned even = (pair[2 * i] & 0xffffu) | (pair[2 * i + 1] << 16);         // column 2 cp, two rows
+        unsigned odd = (pair[2 * i] >> 16) | (pair[2 * i + 1] & 0xffff0000u);      // column 2 cp + 1
+        swap_halves(even, odd);
+        bl.raw[i] = even;
+        bl.raw[8 + i] = odd;
+      }
+    } else {
+      c = lane;
+      const T* p = base + lane;
+      if (j.stride > 1) {
+        AnchorWalk r(blk * 32, j.n_anchor, j.stride);  // wave-uniform
+#pragma unroll
+        for (int i = 0; i < 32; ++i, r.next()) bl.set(i, p[r.src * j.cols]);
+      } else {
+        p += blk * 32 * j.cols;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) bl.set(i, p[i * j.cols]);
+      }
+    }
+    uint8_t* sb = reinterpret_cast<uint8_t*>(scale_lds);
+    if constexpr (FP8) {
+      unsigned w[8];
+      sb[kBlksPerWg * c + lb] = (uint8_t)bl.mxfp8(w);
+      code_lds[c][(2 * lb) ^ (c & 15)] = uint4{w[0], w[1], w[2], w[3]};
+      code_lds[c][(2 * lb + 1) ^ (c & 15)] = uint4{w[4], w[5], w[6], w[7]};
+    } else {
+      unsigned w[4];
+      sb[kBlksPerWg * c + lb] = (uint8_t)bl.mxfp4(w);
+      code_lds[c][lb ^ (c & 7)] = uint4{w[0], w[1], w[2], w[3]};
+    }
+  }
+  __syncthreads();
+  // eight lanes write a column's run, 128 contiguous bytes at a time
+  const int c = tid >> 3;
+  const int64_t col = (int64_t)b * j.cols + cg * kColsPerWg + c;
+  constexpr int kBlkChunks = FP8 ? 2 : 1;
+  uint8_t* cdst = j.codes + (col * nblk + (int64_t)grp * kBlksPerWg) * (16 * kBlkChunks);
+#pragma unroll
+  for (int k = 0; k < kBlkChunks; ++k) {
+    const int ch = (tid & 7) + 8 * k;
+    if (grp * kBlksPerWg + ch / kBlkChunks < nblk)
+      *reinterpret_cast<uint4*>(cdst + ch * 16) = code_lds[c][ch ^ (c & (kChunks - 1))];
+  }
+  if (tid < kColsPerWg)
+    store_scale_run(j.scales + ((int64_t)b * j.cols + cg * kColsPerWg + tid) * nblk + grp * kBlksPerWg, scale_lds[tid],
+                    nblk, grp);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kThreads) void quantize_mxfp4_rows_kernel(const RowsJob j) {
+  quantize_rows<T>(j, blockIdx.x);
+}
+template <typename T, bool FP8>
+__global__ __launch_bounds__(kThreads) void quantize_cols_kernel(const ColsJob j) {
+  quantize_cols<T, FP8>(j, blockIdx.x);
+}
+
+// MXFP4, blocks along rows with transposed output, any number of columns: a
+// thread takes one block, consecutive threads consecutive columns.
+template <typename T>
+__global__ __launch_bounds__(256) void quantize_mxfp4_cols_any_kernel(const T* __restrict__ src, int64_t batch,
+                                                                      int64_t rows, int64_t cols,
+                                                                      uint8_t* __restrict__ codes,
+                                                                      uint8_t* __restrict__ scales, int64_t n_anchor,
+                                                                      int64_t anchor_stride) {
+  const int64_t nblk = rows / 32;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= batch * cols * nblk) return;
+  const int64_t c = t % cols, blk = (t / cols) % nblk, b = t / (cols * nblk);
+  const T* p = src + b * rows * cols + c;
+  Block<T> bl;
+  AnchorWalk r(blk * 32, n_anchor, anchor_stride);
+#pragma unroll
+  for (int i = 0; i < 32; ++i, r.next()) bl.set(i, p[r.src * cols]);
+  unsigned w[4];
+  scales[(b * cols + c) * nblk + blk] = (uint8_t)bl.mxfp4(w);
+  *reinterpret_cast<v4i*>(codes + ((b * cols + c) * nblk + blk) * 16) = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+}
+
+// bf16, blocks along rows with transposed output (V): a thread takes one block
+// of two adjacent columns (one 4-byte load per row; a wave reads 256-byte row
+// segments).  cols % 2 == 0.  (Several blocks per thread, for longer runs of
+// contiguous code bytes, measured slower: fewer waves in flight.)
+__global__ __launch_bounds__(256) void quantize_mxfp4_bf16_cols_kernel(const uint16_t* __restrict__ src, int64_t batch,
+                                                                       int64_t rows, int64_t cols,
+                                                                       uint8_t* __restrict__ codes,
+                                                                       uint8_t* __restrict__ scales, int64_t n_anchor,
+                                                                       int64_t anchor_stride) {
+  const int64_t nblk = rows / 32, npair = cols / 2;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= batch * nblk * npair) return;
+  const int64_t cp = t % npair, blk = (t / npair) % nblk, b = t / (npair * nblk);
+  const uint16_t* base = src + b * rows * cols + 2 * cp;
+  unsigned pair[32];
+  AnchorWalk r(blk * 32, n_anchor, anchor_stride);
+#pragma unroll
+  for (int j = 0; j < 32; ++j, r.next()) pair[j] = *reinterpret_cast<const unsigned*>(base + r.src * cols);
+  unsigned raw0[16], raw1[16];  // column 2 cp and 2 cp + 1, rows in order
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    raw0[i] = (pair[2 * i] & 0xffffu) | (pair[2 * i + 1] << 16);
+    raw1[i] = (pair[2 * i] >> 16) | (pair[2 * i + 1] & 0xffff0000u);
+  }
+  const int64_t col0 = b * cols + 2 * cp;
+  unsigned w[4];
+  scales[col0 * nblk + blk] = (uint8_t)mxfp4_block_bf16(raw0, w);
+  *reinterpret_cast<v4i*>(codes + (col0 * nblk + blk) * 16) = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+  scales[(col0 + 1) * nblk + blk] = (uint8_t)mxfp4_block_bf16(raw1, w);
+  *reinterpret_cast<v4i*>(codes + ((col0 + 1) * nblk + blk) * 16) = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+}
+
+template <typename T>
+__device__ __forceinline__ float load_as_float(const T* p);
+template <>
+__device__ __forceinline__ float load_as_float<float>(const float* p) { return *p; }
+template <>
+__device__ __forceinline__ float load_as_float<uint16_t>(const uint16_t* p) {
+  return __builtin_bit_cast(float, (unsigned)(*p) << 16);
+}
+
 template <typename T, int AXIS>
 __global__ __launch_bounds__(256) void quantize_mxfp8_kernel(const T* __restrict__ src, int64_t batch, int64_t rows,
                                                              int64_t cols, uint8_t* __restrict__ codes,
@@ -435,110 +609,65 @@ __global__ __launch_bounds__(256) void quantize_mxfp8_kernel(const T* __restrict
   scales[(b * outer + o) * nblk + blk] = (uint8_t)ubyte;
 }
 
-// MXFP8 of bf16 blocks along rows with transposed output (V of the FP8 P/V
-// route), staged like the MXFP4 V^T kernel: a workgroup takes 64 columns x 256
-// rows (32 column pairs x 8 blocks, 4-byte row loads), parks its payloads and
-// scale bytes in LDS and writes each column's 8 blocks as one 256-byte run (each
-// store instruction of a wave covers 64 contiguous bytes of 16 columns) and its
-// 8 scale bytes with one store.
-// cols % 64 == 0; blocks past the last are skipped (their threads still meet
-// the barrier).
-__global__ __launch_bounds__(256) void quantize_mxfp8_bf16_cols_staged_kernel(
-    const uint16_t* __restrict__ src, int64_t batch, int64_t rows, int64_t cols, uint8_t* __restrict__ codes,
-    uint8_t* __restrict__ scales) {
-  __shared__ uint4 code_lds[64][16];  // column x 16-byte chunk of its 256-byte run
-  __shared__ uint2 scale_lds[64];      // 8 bytes per column
-  const int64_t nblk = rows / 32, ngrp = (nblk + 7) / 8, ncg = cols / 64;
-  const int64_t cg = blockIdx.x % ncg, grp = (blockIdx.x / ncg) % ngrp, b = blockIdx.x / (ngrp * ncg);
-  const int tid = threadIdx.x, cp = tid % 32, lb = tid / 32;
-  const int64_t blk = grp * 8 + lb;
-  if (blk < nblk) {
-    const uint16_t* base = src + (b * rows + blk * 32) * cols + cg * 64 + 2 * cp;
-    float v0[32], v1[32];
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      const unsigned pr = *reinterpret_cast<const unsigned*>(base + (int64_t)j * cols);
-      v0[j] = __builtin_bit_cast(float, pr << 16);
-      v1[j] = __builtin_bit_cast(float, pr & 0xffff0000u);
-    }
-    unsigned w[8];
-    uint8_t* sb = reinterpret_cast<uint8_t*>(scale_lds);
-    sb[16 * cp + lb] = (uint8_t)mxfp8_block(v0, w);
-    code_lds[2 * cp][2 * lb] = uint4{w[0], w[1], w[2], w[3]};
-    code_lds[2 * cp][2 * lb + 1] = uint4{w[4], w[5], w[6], w[7]};
-    sb[16 * cp + 8 + lb] = (uint8_t)mxfp8_block(v1, w);
-    code_lds[2 * cp + 1][2 * lb] = uint4{w[0], w[1], w[2], w[3]};
-    code_lds[2 * cp + 1][2 * lb + 1] = uint4{w[4], w[5], w[6], w[7]};
-  }
-  __syncthreads();
-  // thread t writes 16-byte chunks (t % 4) + 4 k, k < 4, of column t / 4 (chunk
-  // 2 l + h is half h of block l)
-  const int c = tid / 4, part = tid % 4;
-  const int64_t col = b * cols + cg * 64 + c;
-  uint8_t* cdst = codes + (col * nblk + grp * 8) * 32;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int ch = part + 4 * k;
-    if (grp * 8 + ch / 2 < nblk) *reinterpret_cast<uint4*>(cdst + ch * 16) = code_lds[c][ch];
-  }
-  if (tid < 64) store_scale_run(scales + (b * cols + cg * 64 + tid) * nblk + grp * 8, scale_lds[tid], nblk, grp);
+namespace {
+
+template <typename T>
+hipError_t launch_rows(const RowsJob& j, hipStream_t stream) {
+  const unsigned n = (unsigned)((j.total + kThreads - 1) / kThreads);
+  hipLaunchKernelGGL((quantize_mxfp4_rows_kernel<T>), dim3(n), dim3(kThreads), 0, stream, j);
+  return hipGetLastError();
 }
+
+template <typename T, bool FP8>
+hipError_t launch_cols(const ColsJob& j, int64_t batch, hipStream_t stream) {
+  const int64_t nblk = j.rows / 32;
+  const unsigned n = (unsigned)(batch * (j.cols / kColsPerWg) * ((nblk + kBlksPerWg - 1) / kBlksPerWg));
+  hipLaunchKernelGGL((quantize_cols_kernel<T, FP8>), dim3(n), dim3(kThreads), 0, stream, j);
+  return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t launch_quantize_mxfp4(const void* src, int src_dtype, int64_t batch, int64_t rows, int64_t cols, int axis,
                                  int64_t n_anchor, uint8_t* codes, uint8_t* scales, hipStream_t stream) {
   const int64_t stride = n_anchor > 0 ? rows / n_anchor : 0;
-  const int64_t nblk = axis == 1 ? cols / 32 : rows / 32;
-  const int64_t outer = axis == 1 ? rows : cols;
-  const int64_t total = batch * outer * nblk;
-  const dim3 grid((unsigned)((total + 255) / 256)), block(256);
-  if (src_dtype == 1 && axis == 1) {
-    hipLaunchKernelGGL(quantize_mxfp4_bf16_rows_kernel, grid, block, 0, stream, (const uint16_t*)src, batch, rows, cols,
+  const bool bf16 = src_dtype == 1;
+  if (axis == 1) {
+    const RowsJob j{src, codes, scales, batch * rows * (cols / 32), rows, cols / 32, n_anchor, stride};
+    return bf16 ? launch_rows<uint16_t>(j, stream) : launch_rows<float>(j, stream);
+  }
+  if (cols % kColsPerWg == 0) {  // whole column groups; otherwise lanes of the staged kernel would idle
+    const ColsJob j{src, codes, scales, rows, cols, n_anchor, stride};
+    return bf16 ? launch_cols<uint16_t, false>(j, batch, stream) : launch_cols<float, false>(j, batch, stream);
+  }
+  const int64_t nblk = rows / 32;
+  const bool pairs = bf16 && cols % 2 == 0;  // two columns per thread, 4-byte loads
+  const int64_t threads = batch * nblk * (pairs ? cols / 2 : cols);
+  const dim3 grid((unsigned)((threads + 255) / 256)), block(256);
+  if (pairs)
+    hipLaunchKernelGGL(quantize_mxfp4_bf16_cols_kernel, grid, block, 0, stream, (const uint16_t*)src, batch, rows, cols,
                        codes, scales, n_anchor, stride);
-    return hipGetLastError();
-  }
-  if (src_dtype == 1 && axis == 0 && cols % 64 == 0) {
-    const int64_t groups = batch * (cols / 64) * ((nblk + 7) / 8);
-    hipLaunchKernelGGL(quantize_mxfp4_bf16_cols_staged_kernel, dim3((unsigned)groups), block, 0, stream,
-                       (const uint16_t*)src, batch, rows, cols, codes, scales, n_anchor, stride);
-    return hipGetLastError();
-  }
-  if (src_dtype == 1 && axis == 0 && cols % 2 == 0) {
-    const int64_t threads = batch * nblk * (cols / 2);
-    hipLaunchKernelGGL(quantize_mxfp4_bf16_cols_kernel, dim3((unsigned)((threads + 255) / 256)), block, 0, stream,
-                       (const uint16_t*)src, batch, rows, cols, codes, scales, n_anchor, stride);
-    return hipGetLastError();
-  }
-  if (src_dtype == 0) {
-    if (axis == 1)
-      hipLaunchKernelGGL((quantize_mxfp4_kernel<float, 1>), grid, block, 0, stream, (const float*)src, batch, rows,
-                         cols, codes, scales, n_anchor, stride);
-    else
-      hipLaunchKernelGGL((quantize_mxfp4_kernel<float, 0>), grid, block, 0, stream, (const float*)src, batch, rows,
-                         cols, codes, scales, n_anchor, stride);
-  } else {
-    if (axis == 1)
-      hipLaunchKernelGGL((quantize_mxfp4_kernel<uint16_t, 1>), grid, block, 0, stream, (const uint16_t*)src, batch,
-                         rows, cols, codes, scales, n_anchor, stride);
-    else
-      hipLaunchKernelGGL((quantize_mxfp4_kernel<uint16_t, 0>), grid, block, 0, stream, (const uint16_t*)src, batch,
-                         rows, cols, codes, scales, n_anchor, stride);
-  }
+  else if (bf16)
+    hipLaunchKernelGGL((quantize_mxfp4_cols_any_kernel<uint16_t>), grid, block, 0, stream, (const uint16_t*)src, batch,
+                       rows, cols, codes, scales, n_anchor, stride);
+  else
+    hipLaunchKernelGGL((quantize_mxfp4_cols_any_kernel<float>), grid, block, 0, stream, (const float*)src, batch, rows,
+                       cols, codes, scales, n_anchor, stride);
   return hipGetLastError();
 }
 
 hipError_t launch_quantize_mxfp8(const void* src, int src_dtype, int64_t batch, int64_t rows, int64_t cols, int axis,
                                  uint8_t* codes, uint8_t* scales, hipStream_t stream) {
+  const bool bf16 = src_dtype == 1;
+  if (axis == 0 && cols % kColsPerWg == 0) {
+    const ColsJob j{src, codes, scales, rows, cols, 0, 0};
+    return bf16 ? launch_cols<uint16_t, true>(j, batch, stream) : launch_cols<float, true>(j, batch, stream);
+  }
   const int64_t nblk = axis == 1 ? cols / 32 : rows / 32;
   const int64_t outer = axis == 1 ? rows : cols;
   const int64_t total = batch * outer * nblk;
   const dim3 grid((unsigned)((total + 255) / 256)), block(256);
-  if (src_dtype == 1 && axis == 0 && cols % 64 == 0) {
-    const int64_t groups = batch * (cols / 64) * ((nblk + 7) / 8);
-    hipLaunchKernelGGL(quantize_mxfp8_bf16_cols_staged_kernel, dim3((unsigned)groups), block, 0, stream,
-                       (const uint16_t*)src, batch, rows, cols, codes, scales);
-    return hipGetLastError();
-  }
-  if (src_dtype == 0) {
+  if (!bf16) {
     if (axis == 1)
       hipLaunchKernelGGL((quantize_mxfp8_kernel<float, 1>), grid, block, 0, stream, (const float*)src, batch, rows,
                          cols, codes, scales);

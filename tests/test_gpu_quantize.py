@@ -269,3 +269,92 @@ def test_quantizer_shape_sweep(fa, shape):
                 cg, sg = fa.quantize_mxfp4(xd.cuda(), axis=axis, n_anchor=128)
                 co, so = mxfp4.quantize(workloads.as_f64(xd)[:, perm], axis=axis)
                 assert np.array_equal(sg.cpu().numpy(), so) and np.array_equal(cg.cpu().numpy(), co), (dtype, axis)
+
+
+def _near_boundary_fp32_blocks():
+    """fp32 blocks whose decisions hang on the last bit: values within two ulps of
+    every E2M1 boundary (of r = 6 v / 2^e and of 2 r) on both signs, and blocks
+    tuned by bisection so that the floor / ceiling sum changes sign between
+    neighbouring floats of one element."""
+    bounds = np.array([0.25, 0.75, 1.25, 1.75, 2.5, 3.5, 5.0])
+    blocks = []
+    for b in np.concatenate([bounds / 6, bounds / 12]):
+        centre = np.float32(b)
+        ulps = [centre]
+        for direction in (np.float32(0), np.float32(9)):
+            x = centre
+            for _ in range(2):
+                x = np.nextafter(x, direction)
+                ulps.append(x)
+        vals = np.array(ulps + [-u for u in ulps], dtype=np.float32)
+        for top in (1.0, 0.97, 0.53):           # the block maximum (a power of two has one candidate only)
+            blocks.append(np.concatenate([np.resize(vals, 31), [np.float32(top)]]).astype(np.float32))
+
+    def value(a):
+        k = ((a > 0.25).astype(int) + (a >= 0.75) + (a > 1.25) + (a >= 1.75) + (a > 2.5) + (a >= 3.5) + (a > 5.0))
+        return np.array([0, 0.5, 1, 1.5, 2, 3, 4, 6])[k]
+
+    def delta(v):                               # exact in fp64
+        r = 6.0 * np.abs(v.astype(np.float64))  # the maximum lies in (1/2, 1): 2^e_ceil = 1
+        qc, qf = value(r), value(2 * r)
+        return float(np.sum((2 * qc - qf) * (4 * r - qf - 2 * qc)))
+
+    rng = np.random.default_rng(5)
+    for _ in range(4000):                       # a maximum near 0.6 balances the two candidates
+        if len(blocks) >= 128:
+            break
+        v = (rng.standard_normal(32) * 0.2).clip(-0.58, 0.58).astype(np.float32)
+        v[31] = 0.6
+        lo, hi = np.float32(rng.uniform(0.03, 0.3)), np.float32(rng.uniform(0.3, 0.58))
+        d_lo, d_hi = (delta(np.concatenate([[x], v[1:]]).astype(np.float32)) for x in (lo, hi))
+        if (d_lo < 0) == (d_hi < 0):
+            continue
+        while np.nextafter(lo, hi) < hi:
+            mid = np.float32((np.float64(lo) + np.float64(hi)) / 2)
+            d = delta(np.concatenate([[mid], v[1:]]).astype(np.float32))
+            lo, hi = (mid, hi) if (d < 0) == (d_lo < 0) else (lo, mid)
+        for x in (lo, hi):
+            blocks.append(np.concatenate([[x], v[1:]]).astype(np.float32))
+    assert len(blocks) >= 128
+    return torch.from_numpy(np.stack(blocks[:128]))                          # [128 blocks, 32]
+
+
+@pytest.mark.parametrize("axis,cols", [(-1, 32), (-2, 64), (-2, 8)])
+@pytest.mark.parametrize("shift", [0, -135, 120])
+def test_fp32_decisions_on_the_last_bit(fa, axis, cols, shift):
+    """Every fp32 kernel (rows, staged columns, any columns) over decisions that a
+    rounded product or a rounded sum would take wrongly, also with the block
+    exponent below and near the ends of the E8M0 range."""
+    x = _near_boundary_fp32_blocks()
+    x = torch.ldexp(x, torch.tensor(shift))     # exact but for the subnormals of -135, which are inputs like any other
+    if axis == -1:
+        x = x.reshape(1, 128, 32)
+    else:                                       # block (g, c) = rows 32 g .. 32 g + 31 of column c
+        x = x.reshape(128 // cols, cols, 32).permute(0, 2, 1).reshape(1, 32 * 128 // cols, cols).contiguous()
+    _check(fa, x, axis)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cols", [64, 66, 7])
+@pytest.mark.parametrize("rows,n_anchor", [(96, 3), (96, 48), (160, 160), (352, 11), (512, 1)])
+def test_anchor_walk(fa, dtype, cols, rows, n_anchor):
+    """Anchor order down the columns where a 32-row block holds the end of the
+    anchors, strides from 1 to the whole matrix, every column kernel; and along
+    the rows."""
+    g = torch.Generator().manual_seed(rows + n_anchor + cols)
+    x = torch.randn(2, rows, cols, generator=g).to(dtype)
+    stride = rows // n_anchor
+    idx = np.arange(rows)
+    perm = np.concatenate([idx[idx % stride == 0], idx[idx % stride != 0]])
+    for axis in (-2, -1):
+        if axis == -1 and cols % 32:
+            continue
+        cg, sg = fa.quantize_mxfp4(x.cuda(), axis=axis, n_anchor=n_anchor)
+        co, so = mxfp4.quantize(workloads.as_f64(x)[:, perm], axis=axis)
+        assert np.array_equal(sg.cpu().numpy(), so) and np.array_equal(cg.cpu().numpy(), co)
+
+
+@pytest.mark.parametrize("shape", [(3, 96, 64), (2, 256, 128), (1, 352, 192)])
+def test_mxfp8_staged_fp32(fa, shape):
+    g = torch.Generator().manual_seed(sum(shape))
+    _check8(fa, torch.randn(*shape, generator=g) * torch.exp2(torch.randint(-20, 20, shape, generator=g)), -2)
