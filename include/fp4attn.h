@@ -113,6 +113,21 @@ fp4attn_status fp4attn_quantize_mxfp4_anchored(const void* src, int src_dtype, i
                                                uint8_t* codes, uint8_t* scales, void* stream);
 
 /*
+ * The forward's operands from Q, K and V of one shape and type, in one launch
+ * where it can: exactly the bytes of fp4attn_quantize_mxfp4 of q and k with axis
+ * 1 and of v with axis 0 (v_fp8 = 1: fp4attn_quantize_mxfp8 of v).  n_anchor > 0:
+ * K and V as fp4attn_quantize_mxfp4_anchored, Q in its own order; 0: no anchors.
+ *
+ * Errors: those of the entries above (rows and cols both multiples of 32),
+ * INVALID_ARG if v_fp8 is not 0 or 1; UNSUPPORTED for v_fp8 with n_anchor.
+ */
+fp4attn_status fp4attn_quantize_qkv(const void* q, const void* k, const void* v, int src_dtype,
+                                    int64_t batch, int64_t rows, int64_t cols, int64_t n_anchor,
+                                    int v_fp8, uint8_t* q_codes, uint8_t* q_scales, uint8_t* k_codes,
+                                    uint8_t* k_scales, uint8_t* vt_codes, uint8_t* vt_scales,
+                                    void* stream);
+
+/*
  * Direct-P full-MXFP4 attention forward, noncausal (Sec. "Direct-P", Alg. 2,
  * eqs. affine-code-map, represented-contributions, represented-output).
  *

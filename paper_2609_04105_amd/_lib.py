@@ -27,6 +27,7 @@ SIGNATURES = {
     "fp4attn_quantize_mxfp4": [_c_p, _int, _i64, _i64, _i64, _int, _c_p, _c_p, _c_p],
     "fp4attn_quantize_mxfp8": [_c_p, _int, _i64, _i64, _i64, _int, _c_p, _c_p, _c_p],
     "fp4attn_quantize_mxfp4_anchored": [_c_p, _int, _i64, _i64, _i64, _int, _i64, _c_p, _c_p, _c_p],
+    "fp4attn_quantize_qkv": [_c_p, _c_p, _c_p, _int, _i64, _i64, _i64, _i64, _int] + [_c_p] * 7,
     "fp4attn_forward_mxfp4": [_c_p] * 6 + [_i64] * 4 + [_f32] * 3 + [_c_p, _int, _c_p],
     "fp4attn_forward_bf16": [_c_p] * 3 + [_i64] * 4 + [_f32, _c_p, _int, _c_p],
     "fp4attn_forward_options_init": [ctypes.POINTER(ForwardOptions)],

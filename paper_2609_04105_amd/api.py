@@ -105,11 +105,29 @@ def quantize_mxfp8(x, axis=-1):
     return codes, scales
 
 
+def _one_launch(q, k, v):
+    """Whether Q, K and V can be quantized together: GPU tensors of one shape, type
+    and device (otherwise each is quantized, and checked, by itself)."""
+    return (isinstance(q, torch.Tensor) and isinstance(k, torch.Tensor) and isinstance(v, torch.Tensor)
+            and q.is_cuda and q.dtype in _DTYPES and q.dim() >= 2 and q.dtype == k.dtype == v.dtype
+            and q.shape == k.shape == v.shape and q.device == k.device == v.device
+            and q.is_contiguous() and k.is_contiguous() and v.is_contiguous())
+
+
 def quantize_qkv(q, k, v, anchored=False, pv_fp8=False):
     """Operands of the forward: MXFP4 Q, K along d; V along the sequence
     (transposed), MXFP4 or, with ``pv_fp8``, MXFP8.  ``anchored``: K and V in the
     anchor key order of the guarded forward (128 anchors)."""
     n_anchor = 128 if anchored else 0
+    if _one_launch(q, k, v) and not (anchored and pv_fp8):
+        lead, (rows, cols) = q.shape[:-2], q.shape[-2:]
+        def empty(*shape):
+            return torch.empty(lead + shape, dtype=torch.uint8, device=q.device)
+        out = (empty(rows, cols // 2), empty(rows, cols // 32), empty(rows, cols // 2), empty(rows, cols // 32),
+               empty(cols, rows if pv_fp8 else rows // 2), empty(cols, rows // 32))
+        _launch(q.device, lib.fp4attn_quantize_qkv, _ptr(q), _ptr(k), _ptr(v), _DTYPES[q.dtype], math.prod(lead), rows,
+                cols, n_anchor, 1 if pv_fp8 else 0, *(_ptr(t) for t in out), _stream(q))
+        return out
     qc, qs = quantize_mxfp4(q, axis=-1)
     kc, ks = quantize_mxfp4(k, axis=-1, n_anchor=n_anchor)
     if pv_fp8:

@@ -159,11 +159,7 @@ fp4attn::DirectPArgs directp_args(const uint8_t* q_codes, const uint8_t* q_scale
   return a;
 }
 
-fp4attn_status quantize_common(const void* src, int src_dtype, int64_t batch, int64_t rows, int64_t cols, int axis,
-                               int64_t n_anchor, uint8_t* codes, uint8_t* scales, void* stream, bool fp8 = false) {
-  REQUIRE_PTR(src);
-  REQUIRE_PTR(codes);
-  REQUIRE_PTR(scales);
+fp4attn_status check_quantize(int src_dtype, int64_t batch, int64_t rows, int64_t cols, int axis) {
   if (src_dtype != FP4ATTN_F32 && src_dtype != FP4ATTN_BF16)
     return fail(FP4ATTN_ERR_INVALID_ARG, "src_dtype %d is not FP4ATTN_F32 or FP4ATTN_BF16", src_dtype);
   if (axis != 0 && axis != 1) return fail(FP4ATTN_ERR_INVALID_ARG, "axis %d must be 0 or 1", axis);
@@ -177,6 +173,23 @@ fp4attn_status quantize_common(const void* src, int src_dtype, int64_t batch, in
     return fail(FP4ATTN_ERR_INVALID_ARG, "tensor too large");
   if ((batch * other * (blocked / 32) + 255) / 256 > 0x7fffffff)
     return fail(FP4ATTN_ERR_INVALID_ARG, "tensor too large for one launch");
+  return FP4ATTN_OK;
+}
+
+fp4attn_status check_anchors(int64_t n_anchor, int64_t rows) {
+  if (n_anchor < 1 || rows % n_anchor != 0)
+    return fail(FP4ATTN_ERR_INVALID_ARG, "n_anchor=%lld must be >= 1 and divide rows=%lld", (long long)n_anchor,
+                (long long)rows);
+  return FP4ATTN_OK;
+}
+
+fp4attn_status quantize_common(const void* src, int src_dtype, int64_t batch, int64_t rows, int64_t cols, int axis,
+                               int64_t n_anchor, uint8_t* codes, uint8_t* scales, void* stream, bool fp8 = false) {
+  REQUIRE_PTR(src);
+  REQUIRE_PTR(codes);
+  REQUIRE_PTR(scales);
+  const fp4attn_status st = check_quantize(src_dtype, batch, rows, cols, axis);
+  if (st != FP4ATTN_OK) return st;
   if (fp8)
     return from_hip(fp4attn::launch_quantize_mxfp8(src, src_dtype, batch, rows, cols, axis, codes, scales,
                                                    static_cast<hipStream_t>(stream)),
@@ -208,10 +221,48 @@ fp4attn_status fp4attn_quantize_mxfp8(const void* src, int src_dtype, int64_t ba
 fp4attn_status fp4attn_quantize_mxfp4_anchored(const void* src, int src_dtype, int64_t batch, int64_t rows,
                                                int64_t cols, int axis, int64_t n_anchor, uint8_t* codes,
                                                uint8_t* scales, void* stream) {
-  if (n_anchor < 1 || rows % n_anchor != 0)
-    return fail(FP4ATTN_ERR_INVALID_ARG, "n_anchor=%lld must be >= 1 and divide rows=%lld", (long long)n_anchor,
-                (long long)rows);
+  const fp4attn_status st = check_anchors(n_anchor, rows);
+  if (st != FP4ATTN_OK) return st;
   return quantize_common(src, src_dtype, batch, rows, cols, axis, n_anchor, codes, scales, stream);
+}
+
+fp4attn_status fp4attn_quantize_qkv(const void* q, const void* k, const void* v, int src_dtype, int64_t batch,
+                                    int64_t rows, int64_t cols, int64_t n_anchor, int v_fp8, uint8_t* q_codes,
+                                    uint8_t* q_scales, uint8_t* k_codes, uint8_t* k_scales, uint8_t* vt_codes,
+                                    uint8_t* vt_scales, void* stream) {
+  REQUIRE_PTR(q);
+  REQUIRE_PTR(k);
+  REQUIRE_PTR(v);
+  REQUIRE_PTR(q_codes);
+  REQUIRE_PTR(q_scales);
+  REQUIRE_PTR(k_codes);
+  REQUIRE_PTR(k_scales);
+  REQUIRE_PTR(vt_codes);
+  REQUIRE_PTR(vt_scales);
+  fp4attn_status st = check_quantize(src_dtype, batch, rows, cols, 1);
+  if (st == FP4ATTN_OK) st = check_quantize(src_dtype, batch, rows, cols, 0);
+  if (st == FP4ATTN_OK && n_anchor != 0) st = check_anchors(n_anchor, rows);
+  if (st != FP4ATTN_OK) return st;
+  if (v_fp8 != 0 && v_fp8 != 1) return fail(FP4ATTN_ERR_INVALID_ARG, "v_fp8 must be 0 or 1");
+  if (v_fp8 && n_anchor != 0)
+    return fail(FP4ATTN_ERR_UNSUPPORTED, "the MXFP8 quantizer has no anchor order");
+  fp4attn::QkvArgs a{};
+  a.q = q;
+  a.k = k;
+  a.v = v;
+  a.src_dtype = src_dtype;
+  a.batch = batch;
+  a.rows = rows;
+  a.cols = cols;
+  a.n_anchor = n_anchor;
+  a.v_fp8 = v_fp8;
+  a.q_codes = q_codes;
+  a.q_scales = q_scales;
+  a.k_codes = k_codes;
+  a.k_scales = k_scales;
+  a.vt_codes = vt_codes;
+  a.vt_scales = vt_scales;
+  return from_hip(fp4attn::launch_quantize_qkv(a, static_cast<hipStream_t>(stream)), "quantize launch");
 }
 
 fp4attn_status fp4attn_forward_mxfp4(const uint8_t* q_codes, const uint8_t* q_scales, const uint8_t* k_codes,

@@ -15,6 +15,24 @@ hipError_t launch_quantize_mxfp4(const void* src, int src_dtype, int64_t batch, 
 hipError_t launch_quantize_mxfp8(const void* src, int src_dtype, int64_t batch, int64_t rows, int64_t cols, int axis,
                                  uint8_t* codes, uint8_t* scales, hipStream_t stream);
 
+// Q, K and V of one shape and type; n_anchor > 0: K and V in anchor order.
+struct QkvArgs {
+  const void* q;
+  const void* k;
+  const void* v;
+  int src_dtype;
+  int64_t batch, rows, cols, n_anchor;
+  int v_fp8;  // V as MXFP8 (n_anchor is then 0)
+  uint8_t* q_codes;
+  uint8_t* q_scales;
+  uint8_t* k_codes;
+  uint8_t* k_scales;
+  uint8_t* vt_codes;
+  uint8_t* vt_scales;
+};
+
+hipError_t launch_quantize_qkv(const QkvArgs& a, hipStream_t stream);
+
 struct DirectPArgs {
   const uint8_t* q_codes;
   const uint8_t* q_scales;

@@ -10,10 +10,11 @@
 // too, see mxfp4_block_bf16 and mxfp4_block_f32).  One thread owns one block.
 //
 // What bounds it: memory.  Each value is read once (2 or 4 bytes) and leaves as
-// 17/32 byte (MXFP8: 33/32).  Q, K and V of B2 H16 N4096 d128 in fp32 take 54.7 us
-// (4.2 TB/s; 319 us with the rule's sum and every code decision in fp64); of B1 H32
-// N16384 d128 in bf16 99.2 us (5.1 TB/s; 100.9 us with three 64-bit index divisions
-// per block and two V columns per thread).  A device copy runs at 5.3 TB/s.
+// 17/32 byte (MXFP8: 33/32).  Q, K and V of B2 H16 N4096 d128 in fp32 take 46.6 us
+// (4.9 TB/s; 319 us with the rule's sum and every code decision in fp64); of B1 H32
+// N16384 d128 in bf16 93.7 us (5.4 TB/s; 100.9 us with three launches, three 64-bit
+// index divisions per block and two V columns per thread).  A device copy runs at
+// 5.3 TB/s.
 #include "gfx950.hpp"
 #include "launch.hpp"
 
@@ -509,6 +510,20 @@ __global__ __launch_bounds__(kThreads) void quantize_cols_kernel(const ColsJob j
   quantize_cols<T, FP8>(j, blockIdx.x);
 }
 
+// Q, K and V in one launch: workgroups [0, n_v) take V (the longest of the three
+// for a small call), the next n_q Q, the rest K.  One launch instead of three, and
+// the three fill the chip together: bf16 B3 H10 N1920 d64 21.7 us in three kernels,
+// 10.0 us in one; B1 H32 N16384 d128 99.2 -> 93.7 us; fp32 B2 H16 N4096 d128
+// 54.7 -> 46.6 us.
+template <typename T, bool FP8>
+__global__ __launch_bounds__(kThreads) void quantize_qkv_kernel(const RowsJob q, const RowsJob k, const ColsJob v,
+                                                                unsigned n_v, unsigned n_q) {
+  const unsigned wg = blockIdx.x;
+  if (wg < n_v) quantize_cols<T, FP8>(v, wg);
+  else if (wg < n_v + n_q) quantize_rows<T>(q, wg - n_v);
+  else quantize_rows<T>(k, wg - n_v - n_q);
+}
+
 // MXFP4, blocks along rows with transposed output, any number of columns: a
 // thread takes one block, consecutive threads consecutive columns.
 template <typename T>
@@ -611,18 +626,40 @@ __global__ __launch_bounds__(256) void quantize_mxfp8_kernel(const T* __restrict
 
 namespace {
 
+int64_t workgroups(const RowsJob& j) { return (j.total + kThreads - 1) / kThreads; }
+int64_t workgroups(const ColsJob& j, int64_t batch) {
+  return batch * (j.cols / kColsPerWg) * ((j.rows / 32 + kBlksPerWg - 1) / kBlksPerWg);
+}
+
 template <typename T>
 hipError_t launch_rows(const RowsJob& j, hipStream_t stream) {
-  const unsigned n = (unsigned)((j.total + kThreads - 1) / kThreads);
-  hipLaunchKernelGGL((quantize_mxfp4_rows_kernel<T>), dim3(n), dim3(kThreads), 0, stream, j);
+  hipLaunchKernelGGL((quantize_mxfp4_rows_kernel<T>), dim3((unsigned)workgroups(j)), dim3(kThreads), 0, stream, j);
   return hipGetLastError();
 }
 
+// A launch holds fewer than 2^32 threads; more matrices than that take several.
+constexpr int64_t kMaxWorkgroups = (int64_t(1) << 32) / kThreads - 1;
+
 template <typename T, bool FP8>
-hipError_t launch_cols(const ColsJob& j, int64_t batch, hipStream_t stream) {
-  const int64_t nblk = j.rows / 32;
-  const unsigned n = (unsigned)(batch * (j.cols / kColsPerWg) * ((nblk + kBlksPerWg - 1) / kBlksPerWg));
-  hipLaunchKernelGGL((quantize_cols_kernel<T, FP8>), dim3(n), dim3(kThreads), 0, stream, j);
+hipError_t launch_cols(ColsJob j, int64_t batch, hipStream_t stream) {
+  const int64_t per = workgroups(j, 1), chunk = kMaxWorkgroups / per > 1 ? kMaxWorkgroups / per : 1;
+  const int64_t values = j.rows * j.cols;
+  for (int64_t b = 0; b < batch; b += chunk) {
+    const int64_t n = batch - b < chunk ? batch - b : chunk;
+    hipLaunchKernelGGL((quantize_cols_kernel<T, FP8>), dim3((unsigned)(n * per)), dim3(kThreads), 0, stream, j);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    j.src = static_cast<const T*>(j.src) + n * values;
+    j.codes += n * (FP8 ? values : values / 2);
+    j.scales += n * (values / 32);
+  }
+  return hipSuccess;
+}
+
+template <typename T, bool FP8>
+hipError_t launch_qkv(const RowsJob& q, const RowsJob& k, const ColsJob& v, int64_t batch, hipStream_t stream) {
+  const unsigned n_v = (unsigned)workgroups(v, batch), n_q = (unsigned)workgroups(q);
+  hipLaunchKernelGGL((quantize_qkv_kernel<T, FP8>), dim3(n_v + 2 * n_q), dim3(kThreads), 0, stream, q, k, v, n_v, n_q);
   return hipGetLastError();
 }
 
@@ -683,6 +720,27 @@ hipError_t launch_quantize_mxfp8(const void* src, int src_dtype, int64_t batch, 
                          rows, cols, codes, scales);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_quantize_qkv(const QkvArgs& a, hipStream_t stream) {
+  // one launch where V takes the staged kernel and the three fit one; otherwise one
+  // launch each
+  const int64_t total = a.batch * a.rows * (a.cols / 32), stride = a.n_anchor > 0 ? a.rows / a.n_anchor : 0;
+  const RowsJob q{a.q, a.q_codes, a.q_scales, total, a.rows, a.cols / 32, 0, 0};
+  const RowsJob k{a.k, a.k_codes, a.k_scales, total, a.rows, a.cols / 32, a.n_anchor, stride};
+  const ColsJob v{a.v, a.vt_codes, a.vt_scales, a.rows, a.cols, a.n_anchor, stride};
+  if (a.cols % kColsPerWg != 0 || workgroups(v, a.batch) + 2 * workgroups(q) > kMaxWorkgroups) {
+    hipError_t e = launch_quantize_mxfp4(a.q, a.src_dtype, a.batch, a.rows, a.cols, 1, 0, a.q_codes, a.q_scales, stream);
+    if (e != hipSuccess) return e;
+    e = launch_quantize_mxfp4(a.k, a.src_dtype, a.batch, a.rows, a.cols, 1, a.n_anchor, a.k_codes, a.k_scales, stream);
+    if (e != hipSuccess) return e;
+    return a.v_fp8 ? launch_quantize_mxfp8(a.v, a.src_dtype, a.batch, a.rows, a.cols, 0, a.vt_codes, a.vt_scales, stream)
+                   : launch_quantize_mxfp4(a.v, a.src_dtype, a.batch, a.rows, a.cols, 0, a.n_anchor, a.vt_codes,
+                                           a.vt_scales, stream);
+  }
+  if (a.src_dtype == 1)
+    return a.v_fp8 ? launch_qkv<uint16_t, true>(q, k, v, a.batch, stream) : launch_qkv<uint16_t, false>(q, k, v, a.batch, stream);
+  return a.v_fp8 ? launch_qkv<float, true>(q, k, v, a.batch, stream) : launch_qkv<float, false>(q, k, v, a.batch, stream);
 }
 
 }  // namespace fp4attn

@@ -358,3 +358,23 @@ def test_anchor_walk(fa, dtype, cols, rows, n_anchor):
 def test_mxfp8_staged_fp32(fa, shape):
     g = torch.Generator().manual_seed(sum(shape))
     _check8(fa, torch.randn(*shape, generator=g) * torch.exp2(torch.randint(-20, 20, shape, generator=g)), -2)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("anchored,pv_fp8", [(False, False), (True, False), (False, True)])
+@pytest.mark.parametrize("shape", [(1, 1, 128, 64), (2, 3, 384, 128), (1, 5, 1152, 64), (256, 32), (3, 128, 96)])
+def test_qkv_in_one_launch(fa, dtype, anchored, pv_fp8, shape):
+    """quantize_qkv gives the bytes of the three quantizers: partly filled last
+    workgroups of each part, column counts that cannot share a launch, and inputs
+    of different shapes or types, which are quantized one by one."""
+    g = torch.Generator().manual_seed(len(shape) + shape[-1])
+    q, k, v = (torch.randn(*shape, generator=g).to(dtype).cuda() for _ in range(3))
+    other = torch.float32 if dtype == torch.bfloat16 else torch.bfloat16
+    for q_, k_, v_ in ((q, k, v), (q[..., :128, :].contiguous(), k, v), (q, k, v.to(other))):
+        n = 128 if anchored else 0
+        want = (*fa.quantize_mxfp4(q_), *fa.quantize_mxfp4(k_, n_anchor=n),
+                *(fa.quantize_mxfp8(v_, axis=-2) if pv_fp8 else fa.quantize_mxfp4(v_, axis=-2, n_anchor=n)))
+        got = fa.quantize_qkv(q_, k_, v_, anchored=anchored, pv_fp8=pv_fp8)
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    with pytest.raises(ValueError):
+        fa.quantize_qkv(q, k, v, anchored=True, pv_fp8=True)
