@@ -40,9 +40,9 @@
 // - Denominator c_B: an extra 16x16x128 product of the same P^T register with a
 //   constant indicator operand, so it uses exactly the codes and E8M0 bytes of
 //   PV and costs no vector-ALU work.
-// - K/V tiles of 128 keys are staged in LDS in matrix-operand order (each
-//   lane's 16-byte fragment contiguous): a ring of four tiles filled three
-//   tiles ahead by direct-to-LDS loads.  The key loop is software
+// - K/V tiles of 128 keys are staged in LDS row by row (16-byte chunks swizzled,
+//   see Layout): a ring of four tiles filled three tiles ahead by coalesced
+//   direct-to-LDS loads.  The key loop is software
 //   pipelined two deep: while the vector ALU maps step g+1 to codes, the
 //   matrix unit runs PV of step g and QK of step g+2.  With d = 64 and FP4 P/V
 //   the loop runs one step deep at four waves per SIMD instead.
@@ -92,12 +92,11 @@ struct KParams {
 
 template <int D, bool PV8 = false>
 struct Layout {
-  static constexpr int kCodes = (kBN / 32) * (D / 64) * 1024;  // K fragments [sub][chunk][lane][16 B]
+  static constexpr int kRow = D / 2;                           // bytes of a K row
+  static constexpr int kCodes = kBN * kRow;                    // K rows [key][kRow], 16-byte chunks swizzled
   static constexpr int kScales = (kBN / 32) * 64 * 4;          // [sub][lane] u32
-  // V^T fragments [step][chunk][lane][16 B] (FP8: [step][chunk][half][lane][16 B],
-  // the two 16-byte halves of a lane's 32-byte operand in separate planes, so
-  // each read of a wave is one contiguous 1 KiB)
-  static constexpr int vCodes = (kBN / 64) * (D / 32) * (PV8 ? 2048 : 1024);
+  static constexpr int vRow = PV8 ? kBN : kBN / 2;             // bytes of a V^T row's 128 keys
+  static constexpr int vCodes = D * vRow;                      // V^T rows [d][vRow], 16-byte chunks swizzled
   static constexpr int vScales = (D / 32) * 64 * 4;            // [chunk][lane] u32
   static constexpr int kOff = 0;
   static constexpr int ksOff = kOff + kCodes;
@@ -118,6 +117,25 @@ struct Layout {
 __device__ __forceinline__ int key_of_row(int sub, int m) {
   return 64 * (sub >> 1) + 32 * ((m >> 2) & 1) + 16 * (sub & 1) + 4 * (m >> 3) + (m & 3);
 }
+// Codes lie in LDS row by row, as in global memory, so that four (FP8 V: eight,
+// K at d = 64: two) neighbouring lanes of a copy read one row's contiguous bytes; the
+// 16-byte chunk c of a row sits in slot c ^ swizzle(row).  The swizzles spread each
+// 16 lanes of an operand read (chunk fixed, rows as below) over all 16 bank groups:
+// the K read's rows are keys that differ in bits 0, 1, 2 and 5 (key_of_row), the V^T
+// read's 16 consecutive rows.
+// (In operand order, one lane's 16 bytes from another row each, a copy took about
+// 64 cycles of the address unit per instruction: 1600 cycles per 128-key tile at
+// d = 128, where the two waves of a SIMD work 2260 cycles on it; now 1000.  B1 H32
+// N16384 d128 1294 -> 1267 us, B2 H16 N4096 d128 94.2 -> 91.5 us.)
+template <int D>
+__device__ __forceinline__ int k_swizzle(int key) {
+  return D == 128 ? ((key >> 2) & 1) + 2 * ((key >> 5) & 1) : (key >> 5) & 1;
+}
+template <bool PV8>
+__device__ __forceinline__ int v_swizzle(int row) {
+  return PV8 ? (row >> 1) & 7 : (row >> 2) & 3;
+}
+
 // Inverse: (subtile, operand row) of key k of a 128-key tile.
 __device__ __forceinline__ int sub_of_key(int k) { return 2 * (k >> 6) + ((k >> 4) & 1); }
 __device__ __forceinline__ int row_of_key(int k) { return 8 * ((k >> 2) & 3) + 4 * ((k >> 5) & 1) + (k & 3); }
@@ -162,14 +180,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_buffer(const uint8_t* bas
 }
 
 // One 128-key tile: K and V^T codes copied from global memory straight into an
-// LDS stage in operand order, and its E8M0 words copied raw, then rearranged
-// in LDS by the wave that copied them.
-//   Codes: item i is one 16-byte operand fragment, K items first, then V^T
-//   items; thread tid copies items tid, tid + NT, ...  A wave's 64 lanes copy
-//   64 consecutive fragments, the order in which the direct-to-LDS load writes.
-//   Scales: 64 raw words per block; wave w copies block w % kRawWaves, so
-//   with more waves than blocks two waves write the same bytes to the same
-//   place, and every wave issues the same number of loads per tile.
+// LDS stage row by row, and its E8M0 words copied raw, then put into operand
+// order in LDS by the wave that copied them.
+//   Codes: item i is one 16-byte chunk of a row, K items first, then V^T items;
+//   thread tid copies items tid, tid + NT, ...  A wave's 64 lanes copy 64
+//   consecutive slots, the order in which the direct-to-LDS load writes.
+//   Scales: 64 raw words per block; wave w copies block w.  Waves beyond the
+//   last block copy a block of K's words again (the same bytes to the same
+//   place; contiguous, unlike V^T's, so the cheapest load there is), and every
+//   wave issues the same number of loads per tile.
 // A copy reads one buffer of the (batch, head) at this lane's fixed offset
 // plus a per-tile scalar offset (key0 / 2) * mul (scales: (key0 / 32) * mul);
 // the buffer, the multiplier and the LDS position are fixed per wave.
@@ -207,25 +226,14 @@ struct TileCopy {
       mul[i] = is_k ? D : (PV8 ? 2 : 1);
       lds_off[i] = is_k ? L::kOff + item0 * 16 : L::vOff + (item0 - nK) * 16;
       if (is_k) {
-        const int m = item & 63, rest = item >> 6;
-        const int c = rest % (D / 64), sub = rest / (D / 64);
-        off[i] = key_of_row(sub, m & 31) * (D / 2) + (2 * c + (m >> 5)) * 16;
-      } else if constexpr (PV8) {
-        // One byte per key.  The FP8 operand's k order: lane half h holds keys
-        // 16 h + [0, 16) (bytes 0-15) and 32 + 16 h + [0, 16) (bytes 16-31) of
-        // the 64-key step, while its E8M0 byte still covers keys 32 h + [0, 32).
-        const int vi = item - nK;
-        const int m = vi & 63, hh = (vi >> 6) & 1, rest = vi >> 7;
-        const int cc = rest % (D / 32), s = rest / (D / 32);
-        off[i] = (cc * 32 + (m & 31)) * N + s * 64 + (m >> 5) * 16 + hh * 32;
+        const int key = item / (L::kRow / 16), slot = item % (L::kRow / 16);
+        off[i] = key * L::kRow + 16 * (slot ^ k_swizzle<D>(key));
       } else {
-        const int vi = item - nK;
-        const int m = vi & 63, rest = vi >> 6;
-        const int cc = rest % (D / 32), s = rest / (D / 32);
-        off[i] = (cc * 32 + (m & 31)) * (N / 2) + s * 32 + (m >> 5) * 16;
+        const int vi = item - nK, row = vi / (L::vRow / 16), slot = vi % (L::vRow / 16);
+        off[i] = row * (PV8 ? N : N / 2) + 16 * (slot ^ v_swizzle<PV8>(row));
       }
     }
-    const int rb = wave % kRawWaves, r = rb * 64 + lane;
+    const int rb = wave < kRawWaves ? wave : wave % (L::rawK / 64), r = rb * 64 + lane;
     const bool raw_k = rb * 64 < L::rawK;
     raw_buf = raw_k ? make_buffer(ks, N * (D / 32)) : make_buffer(vs, D * (N / 32));
     raw_mul = raw_k ? D : 1;  // per 32 keys: d / 32 bytes for each of 32 keys, or one byte
@@ -399,6 +407,23 @@ fwd_mxfp4_kernel(const KParams p) {
   const int ntiles = CAUSAL ? (qt + 1) * BM / kBN : N / kBN;  // causal: keys up to the tile's last query
   const int nsteps = 2 * ntiles;  // 64-key steps
 
+  // This lane's chunk of K row key_of_row(sub, lr) for d-chunk c is 2 c + h; subtiles
+  // differ by multiples of 16 keys, which leave the swizzle unchanged.
+  const int key0 = key_of_row(0, lr);
+  int k_lane[D / 64];
+#pragma unroll
+  for (int c = 0; c < D / 64; ++c) k_lane[c] = L::kOff + key0 * L::kRow + 16 * ((2 * c + h) ^ k_swizzle<D>(key0));
+  // Its chunk of V^T row 32 c + lr for step s is 2 s + h.  FP8, one byte per key: lane
+  // half h holds keys 16 h + [0, 16) and 32 + 16 h + [0, 16) of the 64-key step (the
+  // FP8 operand's k order), chunks 4 s + h and 4 s + h + 2, while its E8M0 byte still
+  // covers keys 32 h + [0, 32).
+  int v_lane[2][PV8 ? 2 : 1];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int b = 0; b < (PV8 ? 2 : 1); ++b)
+      v_lane[s][b] = L::vOff + lr * L::vRow + 16 * ((PV8 ? 4 * s + h + 2 * b : 2 * s + h) ^ v_swizzle<PV8>(lr));
+
   // S^T of 64-key step `sl` (0 or 1) of the tile held in `st`: two 32-key blocks.
   auto qk = [&](const uint8_t* st, auto SL_, v16f(&acc)[2]) {
     constexpr int sl = decltype(SL_)::value;
@@ -409,7 +434,7 @@ fwd_mxfp4_kernel(const KParams p) {
       const int ksc = reinterpret_cast<const int*>(st + L::ksOff)[sub * 64 + lane];
       static_for<D / 64>([&](auto C_) {
         constexpr int c = decltype(C_)::value;
-        const v4i kf = *reinterpret_cast<const v4i*>(st + L::kOff + ((sub * (D / 64) + c) * 64 + lane) * 16);
+        const v4i kf = *reinterpret_cast<const v4i*>(st + k_lane[c] + (64 * (sub >> 1) + 16 * (sub & 1)) * L::kRow);
         a = mfma_fp4_32x32x64<2 * c, 2 * c>(kf, qf[c], a, ksc, qsc);
       });
       acc[t] = a;
@@ -424,12 +449,12 @@ fwd_mxfp4_kernel(const KParams p) {
       constexpr int c = decltype(C_)::value;
       const int vsc = reinterpret_cast<const int*>(st + L::vsOff)[c * 64 + lane];
       if constexpr (PV8) {
-        const uint8_t* vp = st + L::vOff + (s * (D / 32) + c) * 2048 + lane * 16;
-        const v4i v0 = *reinterpret_cast<const v4i*>(vp), v1 = *reinterpret_cast<const v4i*>(vp + 1024);
+        const v4i v0 = *reinterpret_cast<const v4i*>(st + v_lane[s][0] + 32 * c * L::vRow);
+        const v4i v1 = *reinterpret_cast<const v4i*>(st + v_lane[s][PV8 ? 1 : 0] + 32 * c * L::vRow);
         const v8i vf = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
         O[c] = mfma_fp8_32x32x64<2 * s, 0>(vf, P, O[c], vsc, u);
       } else {
-        const v4i vf = *reinterpret_cast<const v4i*>(st + L::vOff + ((s * (D / 32) + c) * 64 + lane) * 16);
+        const v4i vf = *reinterpret_cast<const v4i*>(st + v_lane[s][0] + 32 * c * L::vRow);
         O[c] = mfma_fp4_32x32x64<2 * s, 0>(vf, P, O[c], vsc, u);
       }
     });
