@@ -296,7 +296,9 @@ fp4attn_status fp4attn_forward_bf16(const void* q, const void* k, const void* v,
  *              it was resident, and [w][1], the same interval in ticks of the
  *              100 MHz constant clock; entries past the launch's workgroup
  *              count (B*H*N/256 workgroups when 256-row tiles are used) are
- *              left untouched.  Their ratio is the achieved shader clock.
+ *              left untouched, and workgroups past the last entry (small grids
+ *              take 32 or 64 rows per workgroup) record nothing.  Their ratio
+ *              is the achieved shader clock.
  *
  * With n_rows = 0 nothing is dumped (the five dump pointers are ignored and
  * may be NULL) and the launch is the plain forward kernel itself, so wg_clock

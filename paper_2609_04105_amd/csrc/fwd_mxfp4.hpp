@@ -40,12 +40,16 @@
 // - Denominator c_B: an extra 16x16x128 product of the same P^T register with a
 //   constant indicator operand, so it uses exactly the codes and E8M0 bytes of
 //   PV and costs no vector-ALU work.
-// - K/V tiles of 128 keys are staged in LDS row by row (16-byte chunks swizzled,
-//   see Layout): a ring of four tiles filled three tiles ahead by coalesced
-//   direct-to-LDS loads.  The key loop is software
+// - K/V tiles of 128 keys are staged in LDS in matrix-operand order (each
+//   lane's 16-byte fragment contiguous): a ring of four tiles filled three
+//   tiles ahead by direct-to-LDS loads.  The key loop is software
 //   pipelined two deep: while the vector ALU maps step g+1 to codes, the
 //   matrix unit runs PV of step g and QK of step g+2.  With d = 64 and FP4 P/V
 //   the loop runs one step deep at four waves per SIMD instead.
+// - Small grids split the keys of a query tile among 2, 4 or 8 waves of the
+//   workgroup, each taking one 64-key step in turn, and merge their sums in LDS:
+//   codes do not depend on the reference and the merge scales by exact powers of
+//   two, so only the order of the fp32 sums differs.
 // - Workgroups are remapped so that the query tiles of one head run on one XCD
 //   and share its L2 copy of that head's K/V.
 #pragma once
@@ -88,6 +92,7 @@ struct KParams {
   int32_t* row_m;
   float* row_d;
   unsigned long long* wg_clock;
+  int n_clock;  // workgroups that have an entry in wg_clock
 };
 
 template <int D, bool PV8 = false>
@@ -142,8 +147,13 @@ __device__ __forceinline__ int row_of_key(int k) { return 8 * ((k >> 2) & 3) + 4
 
 // Direct-to-LDS buffer copies: lane l's 16 (4) bytes at byte soff + off of the
 // buffer `rsrc` land at LDS byte address `lds` + 16 l (4 l); `lds` travels in
-// M0, and one wait state separates its write from the load.  Bytes past the
-// buffer's end read as zero, so a copy past the last tile is harmless.
+// M0, and one wait state separates its write from the load.  The instruction between
+// them copies the tile's offset to another scalar register: should the compiler
+// take the offset through v_readfirstlane right before, the load would read a scalar
+// register that a vector instruction has just written, which needs five wait
+// states, and its hazard checks do not look into the assembly.  Bytes past the
+// buffer's end read as zero (offset and scalar offset together), so a copy past the
+// last tile is harmless.
 // Written as inline assembly so that the compiler counts neither the loads
 // nor the LDS they write (it would otherwise wait for every copy in flight
 // before each LDS read); the kernel waits for its own copies with vm_wait
@@ -151,13 +161,17 @@ __device__ __forceinline__ int row_of_key(int k) { return 8 * ((k >> 2) & 3) + 4
 // (`lds` and `soff` are wave-uniform; reading them from the first lane keeps
 // them in scalar registers whatever the compiler's uniformity analysis says.)
 __device__ __forceinline__ void lds_copy16(unsigned lds, __amdgpu_buffer_rsrc_t rsrc, int soff, unsigned off) {
-  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(off), "s"(rsrc),
-               "s"(__builtin_amdgcn_readfirstlane(soff)), "{m0}"(__builtin_amdgcn_readfirstlane(lds))
+  int so;
+  asm volatile("s_mov_b32 %0, %3\n\tbuffer_load_dwordx4 %1, %2, %0 offen lds"
+               : "=&s"(so)
+               : "v"(off), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff)), "{m0}"(__builtin_amdgcn_readfirstlane(lds))
                : "memory");
 }
 __device__ __forceinline__ void lds_copy4(unsigned lds, __amdgpu_buffer_rsrc_t rsrc, int soff, unsigned off) {
-  asm volatile("s_nop 0\n\tbuffer_load_dword %0, %1, %2 offen lds" ::"v"(off), "s"(rsrc),
-               "s"(__builtin_amdgcn_readfirstlane(soff)), "{m0}"(__builtin_amdgcn_readfirstlane(lds))
+  int so;
+  asm volatile("s_mov_b32 %0, %3\n\tbuffer_load_dword %1, %2, %0 offen lds"
+               : "=&s"(so)
+               : "v"(off), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff)), "{m0}"(__builtin_amdgcn_readfirstlane(lds))
                : "memory");
 }
 // Wait until at most n of this wave's vector-memory operations are in flight.
@@ -177,6 +191,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_buffer(const uint8_t* bas
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
   uint8_t* b = (uint8_t*)(((uint64_t)hi << 32) | lo);
   return __builtin_amdgcn_make_buffer_rsrc(b, (short)0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+
+// Both accumulators are formed here and not moved below (emits nothing).  Device
+// code only: a 512-bit operand does not pass the host compiler's asm checks.
+__device__ __forceinline__ void pin(const v16f& a, const v16f& b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" ::"v"(a), "v"(b));
+#endif
 }
 
 // One 128-key tile: K and V^T codes copied from global memory straight into an
@@ -241,7 +263,16 @@ struct TileCopy {
     raw_off = raw_k ? 4 * r : (r - L::rawK) * (N / 32);
   }
 
-  // Fetch the tile of keys [key0, key0 + 128) into stage `st`.
+  // Fetch TPS tiles, keys [key0, key0 + 128 TPS), into stage `st`.
+  template <int TPS>
+  __device__ __forceinline__ void issue_tiles(uint8_t* st, int key0) const {
+#pragma unroll
+    for (int i = 0; i < TPS; ++i) issue(st + i * L::stage, key0 + i * kBN);
+  }
+
+  // Fetch the tile of keys [key0, key0 + 128) into stage `st`.  (Past the end the
+  // buffer's bounds check gives zeros, in a place nobody reads; taking the last
+  // tile again instead cost 0.8 %.)
   __device__ __forceinline__ void issue(uint8_t* st, int key0) const {
     const unsigned lds = lds_address(st);
     const int half = key0 >> 1;
@@ -255,6 +286,11 @@ struct TileCopy {
   // shifted by one byte, at [sub][row + 32] (lanes 0..31 take scale bytes 0 and 2
   // of a word, lanes 32..63 bytes 1 and 3); V^T words likewise per 32-row chunk.
   // Reads only raw words this wave copied itself.
+  template <int TPS>
+  __device__ __forceinline__ static void arrange_tiles(uint8_t* st, int tid) {
+#pragma unroll
+    for (int i = 0; i < TPS; ++i) arrange(st + i * L::stage, tid);
+  }
   __device__ __forceinline__ static void arrange(uint8_t* st, int tid) {
     const int wave = tid >> 6, r = tid;  // wave w < kRawWaves arranges block w
     if (wave >= kRawWaves) return;
@@ -280,45 +316,53 @@ struct TileCopy {
   }
 };
 
+// Key split: KS waves share one query tile, each taking one 64-key step of every
+// KS / 2 key tiles, and merge their sums at the end; a workgroup then has QG
+// query tiles and QG * KS waves.
+//
 // The FP4 P/V routes with d = 64 pipeline the key loop one step deep (one S^T
-// buffer, one P operand) to fit 128 registers: four waves per SIMD, i.e. four
-// four-wave or two eight-wave workgroups of 40 KiB LDS per CU.
-template <int D, int NW, int VAR>
+// buffer, one P operand) to fit 128 registers: four waves per SIMD.
+template <int D, int VAR>
 constexpr bool kOneBuffer = D == 64 && (VAR & kPV8) == 0;
+// Key tiles per LDS stage, and stages in the ring.
+template <int KS>
+constexpr int kTilesPerStage = KS > 2 ? KS / 2 : 1;
+constexpr int kLdsBytes = 160 * 1024;
+template <int D, int KS, int VAR>
+constexpr int kFit = kLdsBytes / (kTilesPerStage<KS> * Layout<D, (VAR & kPV8) != 0>::stage);
+template <int D, int QG, int KS, int VAR>
+constexpr int kRing = kFit<D, KS, VAR> < kStages ? kFit<D, KS, VAR> : kStages;
+// Shapes that exist: at least two stages must fit (not FP8 V with d = 128 and KS = 8).
+template <int D, int KS, int VAR>
+constexpr bool kHasShape = (kFit<D, KS, VAR>) >= 2;
+// One step deep: d = 64 (above), and where the ring holds two stages only.
+template <int D, int QG, int KS, int VAR>
+constexpr bool kOneDeep = kOneBuffer<D, VAR> || kRing<D, QG, KS, VAR> == 2;
 // Two waves per SIMD, except where the LDS ring allows one workgroup of four
 // waves per CU only (FP8 V tiles with d = 128: 108 KiB), and four for the
 // one-buffer form above.
-template <int D, int NW, int VAR>
-constexpr int kMinWaves = (VAR & kPV8) ? ((NW == 4 && D == 128) ? 1 : 2)
-                                       : (kOneBuffer<D, NW, VAR> ? 4 : ((D == 64 && NW == 4) ? 3 : 2));
-template <int D, int NW, int VAR>
-constexpr int kMaxWaves = kMinWaves<D, NW, VAR> > 2 ? kMinWaves<D, NW, VAR> : 2;
+template <int D, int QG, int KS, int VAR>
+constexpr int kMinWaves = (VAR & kPV8) ? ((QG * KS == 4 && D == 128) ? 1 : 2)
+                                       : (kOneBuffer<D, VAR> ? (KS > 2 ? 2 : 4) : 2);
+template <int D, int QG, int KS, int VAR>
+constexpr int kMaxWaves = kMinWaves<D, QG, KS, VAR> > 2 ? kMinWaves<D, QG, KS, VAR> : 2;
 
-template <int D, int NW, bool DUMP, int EX2, int VAR>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(kMinWaves<D, NW, VAR>, kMaxWaves<D, NW, VAR>))) void
+template <int D, int QG, int KS, bool DUMP, int EX2, int VAR>
+__global__ __launch_bounds__(QG * KS * 64)
+__attribute__((amdgpu_waves_per_eu(kMinWaves<D, QG, KS, VAR>, kMaxWaves<D, QG, KS, VAR>))) void
 fwd_mxfp4_kernel(const KParams p) {
+  constexpr int NW = QG * KS;
   constexpr bool PV8 = (VAR & kPV8) != 0;  // FP8 (E4M3) P and V payloads
   constexpr bool GUARD = (VAR & 7) == kVarGuard, CAUSAL = (VAR & 7) == kVarCausal;
   static_assert(!(PV8 && (GUARD || EX2 != 0)), "the FP8 route takes the exponential on every key");
   using POp = std::conditional_t<PV8, v8i, v4i>;  // a lane's 32 P payloads
   static_assert(EX2 == 0 || EX2 == 1 || EX2 == 2 || EX2 == 4 || EX2 == 8 || EX2 == 16, "pairs per 32-key block");
   using L = Layout<D, (VAR & kPV8) != 0>;
-  constexpr int BM = NW * 32;
-  // The LDS ring: one array per stage, so that the compiler tracks the
-  // direct-to-LDS copies per stage and waits for none of them before reading
-  // another stage.
-  __shared__ __attribute__((aligned(16))) uint8_t ring0[L::stage];
-  __shared__ __attribute__((aligned(16))) uint8_t ring1[L::stage];
-  __shared__ __attribute__((aligned(16))) uint8_t ring2[L::stage];
-  __shared__ __attribute__((aligned(16))) uint8_t ring3[L::stage];
-  static_assert(kStages == 4, "one array per ring stage");
-  auto ring = [&](auto B_) -> uint8_t* {
-    constexpr int b = decltype(B_)::value % kStages;
-    if constexpr (b == 0) return ring0;
-    else if constexpr (b == 1) return ring1;
-    else if constexpr (b == 2) return ring2;
-    else return ring3;
-  };
+  constexpr int BM = QG * 32;
+  // The LDS ring; the merge of a key split reuses it.
+  constexpr int TPS = kTilesPerStage<KS>, NST = kRing<D, QG, KS, VAR>;
+  __shared__ __attribute__((aligned(16))) uint8_t ring_mem[NST * TPS * L::stage];
+  auto ring = [&](auto B_) -> uint8_t* { return ring_mem + (decltype(B_)::value % NST) * (TPS * L::stage); };
   using I0 = std::integral_constant<int, 0>;
 
   const int tid = threadIdx.x;
@@ -336,7 +380,9 @@ fwd_mxfp4_kernel(const KParams p) {
     qt = lin % p.n_qtiles;
   }
   const int N = p.N;
-  const int qrow = qt * BM + wave * 32 + lr;
+  // Waves kg * QG + qg: query tile qg of the workgroup, key group kg.
+  const int qg = KS == 1 ? wave : wave % QG, kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / QG;
+  const int qrow = qt * BM + qg * 32 + lr;
 
   const uint8_t* kc = p.kc + (size_t)bh * N * (D / 2);
   const uint8_t* ks = p.ks + (size_t)bh * N * (D / 32);
@@ -404,9 +450,14 @@ fwd_mxfp4_kernel(const KParams p) {
   asm volatile("" : "+v"(na8));
   float Rref = 0.0f;     // guard: fixed row reference from the anchor tile (Alg. 3)
 
-  const int ntiles = CAUSAL ? (qt + 1) * BM / kBN : N / kBN;  // causal: keys up to the tile's last query
+  const int ntiles = CAUSAL ? ((qt + 1) * BM + kBN - 1) / kBN : N / kBN;  // causal: keys up to the tile's last query
   const int nsteps = 2 * ntiles;  // 64-key steps
 
+  // A key group reads step kg % 2 of tile kg / 2 of each stage (KS = 1: both steps
+  // in turn, named by the compile-time arguments below).
+  const int ko = KS == 1 ? 0 : (kg >> 1) * L::stage + (kg & 1) * (64 * L::kRow);
+  const int kso = KS == 1 ? 0 : (kg >> 1) * L::stage + (kg & 1) * 512;
+  const int vso = KS == 1 ? 0 : (kg >> 1) * L::stage + (kg & 1) * 2;
   // This lane's chunk of K row key_of_row(sub, lr) for d-chunk c is 2 c + h; subtiles
   // differ by multiples of 16 keys, which leave the swizzle unchanged.
   const int key0 = key_of_row(0, lr);
@@ -417,29 +468,32 @@ fwd_mxfp4_kernel(const KParams p) {
   // half h holds keys 16 h + [0, 16) and 32 + 16 h + [0, 16) of the 64-key step (the
   // FP8 operand's k order), chunks 4 s + h and 4 s + h + 2, while its E8M0 byte still
   // covers keys 32 h + [0, 32).
-  int v_lane[2][PV8 ? 2 : 1];
+  int v_lane[KS == 1 ? 2 : 1][PV8 ? 2 : 1];
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
+  for (int i = 0; i < (KS == 1 ? 2 : 1); ++i)
 #pragma unroll
-    for (int b = 0; b < (PV8 ? 2 : 1); ++b)
-      v_lane[s][b] = L::vOff + lr * L::vRow + 16 * ((PV8 ? 4 * s + h + 2 * b : 2 * s + h) ^ v_swizzle<PV8>(lr));
+    for (int b = 0; b < (PV8 ? 2 : 1); ++b) {
+      const int s = KS == 1 ? i : kg & 1, chunk = PV8 ? 4 * s + h + 2 * b : 2 * s + h;
+      v_lane[i][b] = (KS == 1 ? 0 : (kg >> 1) * L::stage) + L::vOff + lr * L::vRow + 16 * (chunk ^ v_swizzle<PV8>(lr));
+    }
 
   // S^T of 64-key step `sl` (0 or 1) of the tile held in `st`: two 32-key blocks.
-  auto qk = [&](const uint8_t* st, auto SL_, v16f(&acc)[2]) {
+  auto qk_at = [&](const uint8_t* st, auto SL_, v16f(&acc)[2], int ko, int kso) {
     constexpr int sl = decltype(SL_)::value;
     static_for<2>([&](auto T_) {
       constexpr int t = decltype(T_)::value;
       constexpr int sub = 2 * sl + t;
       v16f a = v16f{};
-      const int ksc = reinterpret_cast<const int*>(st + L::ksOff)[sub * 64 + lane];
+      const int ksc = reinterpret_cast<const int*>(st + kso + L::ksOff)[sub * 64 + lane];
       static_for<D / 64>([&](auto C_) {
         constexpr int c = decltype(C_)::value;
-        const v4i kf = *reinterpret_cast<const v4i*>(st + k_lane[c] + (64 * (sub >> 1) + 16 * (sub & 1)) * L::kRow);
+        const v4i kf = *reinterpret_cast<const v4i*>(st + ko + k_lane[c] + (64 * (sub >> 1) + 16 * (sub & 1)) * L::kRow);
         a = mfma_fp4_32x32x64<2 * c, 2 * c>(kf, qf[c], a, ksc, qsc);
       });
       acc[t] = a;
     });
   };
+  auto qk = [&](const uint8_t* st, auto SL_, v16f(&acc)[2]) { qk_at(st, SL_, acc, ko, kso); };
 
   // PV of step `s` (0 or 1) of the tile held in `st`, and the represented
   // denominator from the same P^T operand and E8M0 bytes.
@@ -447,7 +501,9 @@ fwd_mxfp4_kernel(const KParams p) {
     constexpr int s = decltype(S_)::value;
     static_for<D / 32>([&](auto C_) {
       constexpr int c = decltype(C_)::value;
-      const int vsc = reinterpret_cast<const int*>(st + L::vsOff)[c * 64 + lane];
+      // a key split reads the two bytes of its step (lane half h in byte 0)
+      const int vsc = KS == 1 ? reinterpret_cast<const int*>(st + L::vsOff)[c * 64 + lane]
+                              : (int)*reinterpret_cast<const uint16_t*>(st + vso + L::vsOff + (c * 64 + lane) * 4);
       if constexpr (PV8) {
         const v4i v0 = *reinterpret_cast<const v4i*>(st + v_lane[s][0] + 32 * c * L::vRow);
         const v4i v1 = *reinterpret_cast<const v4i*>(st + v_lane[s][PV8 ? 1 : 0] + 32 * c * L::vRow);
@@ -616,7 +672,7 @@ fwd_mxfp4_kernel(const KParams p) {
   // (register r of subtile t) for query qrow; keys after the query become -inf.
   // Only steps that reach past the wave's first query need it (wave-uniform).
   auto causal_mask = [&](v16f(&acc)[2], int g) {
-    if (64 * g + 63 > qt * BM + wave * 32) {
+    if (64 * g + 63 > qt * BM + qg * 32) {
       const int lim = qrow - (64 * g + 32 * h);  // last visible offset in this lane's block
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -631,23 +687,109 @@ fwd_mxfp4_kernel(const KParams p) {
   // may still be in flight), puts the E8M0 words it copied into operand order,
   // and after the barrier fetches tile t+3 into the stage of tile t-1, which
   // every wave has finished reading.  Every publish fetches exactly one tile
-  // (past the end: bounds-checked bytes, zero past each buffer's end, into a
-  // stage nobody reads), so a wave's vmcnt always counts the same loads.  In 64-key step g the matrix unit runs
+  // (past the end: bounds-checked bytes, into a stage nobody reads), so a wave's
+  // vmcnt always counts the same loads.  In 64-key step g the matrix unit runs
   // PV of step g and QK of step g+2 while the vector ALU runs Direct-P of step
   // g+1.  Steps are unrolled eight at a time (four tiles), so every LDS stage is
   // a compile-time constant.
   using Copy = TileCopy<D, NW, PV8>;
-  constexpr int kBatch = Copy::kLoads;
+  constexpr int kBatch = TPS * Copy::kLoads;
   Copy copy;
   copy.init(kc, ks, vc, vs, N, tid);
-  copy.issue(ring(I0{}), 0);
-  copy.issue(ring(std::integral_constant<int, 1>{}), kBN);
-  copy.issue(ring(std::integral_constant<int, 2>{}), 2 * kBN);
-  vm_wait<2 * kBatch>();  // tile 0 has landed
-  Copy::arrange(ring(I0{}), tid);
-  __syncthreads();
+  if constexpr (KS == 1) {
+    copy.issue(ring(I0{}), 0);
+    copy.issue(ring(std::integral_constant<int, 1>{}), kBN);
+    copy.issue(ring(std::integral_constant<int, 2>{}), 2 * kBN);
+    vm_wait<2 * kBatch>();  // tile 0 has landed
+    Copy::arrange(ring(I0{}), tid);
+    __syncthreads();
+  }
 
-  if constexpr (kOneBuffer<D, NW, VAR>) {
+  if constexpr (KS > 1) {
+    // Key split.  A wave has one step in each stage, so PV of stage t is done
+    // before the barrier that publishes the next stage it reads, and that barrier
+    // frees stage t: the ring is refilled one whole turn ahead.
+    constexpr bool ONE = kOneDeep<D, QG, KS, VAR>;
+    constexpr int AHEAD = ONE ? 1 : 2;            // stage t publishes stage t + AHEAD
+    constexpr int kFly = (NST - 1 - AHEAD) * kBatch;  // copies that may be in flight then
+    const int nst = (ntiles + TPS - 1) / TPS;     // stages
+    const int tk = kg >> 1, sk = kg & 1;
+    const int mine = (ntiles - tk + TPS - 1) / TPS;  // stages that hold a tile of this wave: nst or nst - 1
+    auto step_of = [&](int t) { return 2 * (t * TPS + tk) + sk; };  // 64-key step of stage t
+    static_for<NST>([&](auto I_) { copy.template issue_tiles<TPS>(ring(I_), decltype(I_)::value * TPS * kBN); });
+    vm_wait<(NST - AHEAD) * kBatch>();
+    static_for<AHEAD>([&](auto I_) { Copy::template arrange_tiles<TPS>(ring(I_), tid); });
+    __syncthreads();
+
+    v16f S[ONE ? 1 : 2][2];
+    POp P[ONE ? 1 : 2];
+    int u[ONE ? 1 : 2];
+    if constexpr (GUARD) {
+      // Anchor (Alg. 3, steps 1-2) over both steps of the first key tile
+      float am = -__builtin_inff();
+      static_for<2>([&](auto T_) {
+        qk_at(ring(I0{}), T_, S[0], 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) am = fmaxf(fmaxf(am, S[0][0][r]), S[0][1][r]);
+      });
+      unsigned ma = as_uint(am), mb = ma;
+      swap_halves(ma, mb);
+      {
+#pragma clang fp contract(off)
+        const float Y = fmaxf(as_float(ma), as_float(mb)) * p.c_y;
+        Rref = Y + p.margin;
+      }
+    }
+    if (mine > 0) {
+      qk(ring(I0{}), I0{}, S[0]);
+      if constexpr (CAUSAL) causal_mask(S[0], step_of(0));
+      directp(S[0], step_of(0), P[0], u[0], std::false_type{});
+      if constexpr (!ONE) {
+        if (mine > 1) qk(ring(std::integral_constant<int, 1>{}), I0{}, S[1]);
+      }
+    }
+    auto split_step = [&](auto J_, auto TAIL_, int t) {
+      constexpr int j = decltype(J_)::value;
+      constexpr bool guard = decltype(TAIL_)::value;
+      constexpr int cur = ONE ? 0 : j % 2, nxt = ONE ? 0 : 1 - cur;
+      using b_cur = std::integral_constant<int, j>;
+      using b_new = std::integral_constant<int, j + AHEAD>;
+      if (!guard || t < mine) pv(ring(b_cur{}), I0{}, P[cur], u[cur]);
+      if constexpr (!ONE) {
+        if (!guard || t + 1 < mine) {
+          if constexpr (CAUSAL && guard) causal_mask(S[nxt], step_of(t + 1));
+          directp(S[nxt], step_of(t + 1), P[nxt], u[nxt], std::bool_constant<!guard>{});
+        }
+      }
+      vm_wait<kFly>();  // stage t + AHEAD has landed
+      if (!guard || t + AHEAD < nst) Copy::template arrange_tiles<TPS>(ring(b_new{}), tid);
+      __syncthreads();
+      copy.template issue_tiles<TPS>(ring(b_cur{}), (t + NST) * TPS * kBN);
+      if (!guard || t + AHEAD < mine) {
+        auto& S_out = S[cur];
+        qk(ring(b_new{}), I0{}, S_out);
+        if constexpr (ONE) {
+          if constexpr (CAUSAL && guard) causal_mask(S[0], step_of(t + 1));
+          directp(S[0], step_of(t + 1), P[0], u[0], std::false_type{});
+        } else {
+          pin(S_out[0], S_out[1]);  // issue QK in this step
+        }
+      }
+    };
+    // The tail group holds the steps in which a wave may lack work: the last
+    // AHEAD stages, one more where the last stage may be partly filled.  A masked
+    // stage (causal: the last one) is mapped in the step before it.
+    constexpr int kLeftS = AHEAD + (TPS > 1 ? 1 : 0) + (CAUSAL && AHEAD == 1 && TPS == 1 ? 1 : 0);
+    constexpr int kUnroll = NST % 2 && !ONE ? 2 * NST : NST;
+    int t0 = 0;
+    for (; t0 + kUnroll <= nst - kLeftS; t0 += kUnroll) {
+      static_for<kUnroll>([&](auto J_) { split_step(J_, std::false_type{}, t0 + decltype(J_)::value); });
+    }
+    static_for<kUnroll + kLeftS>([&](auto J_) {
+      const int t = t0 + decltype(J_)::value;
+      if (t < nst) split_step(J_, std::true_type{}, t);
+    });
+  } else if constexpr (kOneBuffer<D, VAR>) {
     // One step deep: step g runs PV(g), then QK(g+1) and its code map, which
     // waits for those products; the other waves of the SIMD fill the wait.  The
     // tile that QK(g+1) reads first is published in the step before it (the
@@ -805,34 +947,94 @@ fwd_mxfp4_kernel(const KParams p) {
     const float d_lo = lane_read(Dacc[0], lane & 15), d_hi = lane_read(Dacc[1], lane & 15);
     Dfin = (lane & 16) ? d_hi : d_lo;
   }
+  // Quad q of the output: registers 4 (q % 4) .. + 3 of O[q / 4], columns
+  // 32 (q / 4) + 8 (q % 4) + 4 h .. + 3.  After a key split each wave finishes
+  // kQuads of them.
+  constexpr int kQuads = D / 8 / KS;
+  v4f own[kQuads];
+  auto quad = [&](auto Q_) {
+    constexpr int q = decltype(Q_)::value;
+    return v4f{O[q / 4][4 * (q % 4)], O[q / 4][4 * (q % 4) + 1], O[q / 4][4 * (q % 4) + 2], O[q / 4][4 * (q % 4) + 3]};
+  };
+  if constexpr (KS == 1) {
+    static_for<kQuads>([&](auto Q_) { own[decltype(Q_)::value] = quad(Q_); });
+  } else {
+    // Merge of the key groups: the largest reference M (the guard's is fixed),
+    // every group's sums scaled to it by an exact power of two, then added.  Each
+    // wave sends the quads it does not finish through LDS.
+    float* md = reinterpret_cast<float*>(ring_mem);  // [kg][qg][M, D][32]
+    v4f* parts = reinterpret_cast<v4f*>(ring_mem + KS * QG * 256);  // [qg][finishing kg][source][quad][lane]
+    static_assert(KS * QG * 256 + QG * KS * (KS - 1) * kQuads * 1024 <= NST * TPS * L::stage, "the merge fits the ring");
+    __syncthreads();  // every wave has read its last stage
+    if (h == 0) {
+      md[((kg * QG + qg) * 2) * 32 + lr] = Mref;
+      md[((kg * QG + qg) * 2 + 1) * 32 + lr] = Dfin;
+    }
+    __syncthreads();
+    float M = Mref;
+    if constexpr (!GUARD) {
+#pragma unroll
+      for (int k = 0; k < KS; ++k) M = fmaxf(M, md[((k * QG + qg) * 2) * 32 + lr]);
+      const int sh = (int)(Mref - M);
+#pragma unroll
+      for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) O[c][r] = ldexpf(O[c][r], sh);
+    }
+    Dfin = 0.0f;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      const float m = md[((k * QG + qg) * 2) * 32 + lr], d = md[((k * QG + qg) * 2 + 1) * 32 + lr];
+      Dfin += GUARD ? d : ldexpf(d, (int)(m - M));
+    }
+    Mref = M;
+    static_for<KS>([&](auto F_) {  // F: the group that finishes these quads
+      constexpr int f = decltype(F_)::value;
+      if (kg == f) {
+        static_for<kQuads>([&](auto Q_) {
+          constexpr int q = decltype(Q_)::value;
+          own[q] = quad(std::integral_constant<int, f * kQuads + q>{});
+        });
+      } else {
+        v4f* dst = parts + ((qg * KS + f) * (KS - 1) + (kg > f ? kg - 1 : kg)) * (kQuads * 64) + lane;
+        static_for<kQuads>([&](auto Q_) {
+          constexpr int q = decltype(Q_)::value;
+          dst[q * 64] = quad(std::integral_constant<int, f * kQuads + q>{});
+        });
+      }
+    });
+    __syncthreads();
+    const v4f* src = parts + (qg * KS + kg) * (KS - 1) * (kQuads * 64) + lane;
+#pragma unroll
+    for (int k = 0; k < KS - 1; ++k)
+#pragma unroll
+      for (int q = 0; q < kQuads; ++q) own[q] += src[(k * kQuads + q) * 64];
+  }
   // O = acc / (6 D) for E2M1 payloads (P and V each carry 1/6); FP8 payloads carry none
   const float inv = 1.0f / ((PV8 ? 1.0f : 6.0f) * Dfin);
   const size_t orow = ((size_t)bh * N + qrow) * D;
 #pragma unroll
-  for (int c = 0; c < D / 32; ++c) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col = 32 * c + 8 * g + 4 * h;
-      const float o0 = O[c][4 * g] * inv, o1 = O[c][4 * g + 1] * inv;
-      const float o2 = O[c][4 * g + 2] * inv, o3 = O[c][4 * g + 3] * inv;
-      if (p.out_bf16) {
-        typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-        const unsigned w0 = __builtin_bit_cast(unsigned, bf2{(__bf16)o0, (__bf16)o1});
-        const unsigned w1 = __builtin_bit_cast(unsigned, bf2{(__bf16)o2, (__bf16)o3});
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(p.out) + orow + col) = uint2{w0, w1};
-      } else {
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.out) + orow + col) = float4{o0, o1, o2, o3};
-      }
+  for (int i = 0; i < kQuads; ++i) {
+    const int q = kg * kQuads + i;
+    const int col = 32 * (q >> 2) + 8 * (q & 3) + 4 * h;
+    const float o0 = own[i][0] * inv, o1 = own[i][1] * inv, o2 = own[i][2] * inv, o3 = own[i][3] * inv;
+    if (p.out_bf16) {
+      typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+      const unsigned w0 = __builtin_bit_cast(unsigned, bf2{(__bf16)o0, (__bf16)o1});
+      const unsigned w1 = __builtin_bit_cast(unsigned, bf2{(__bf16)o2, (__bf16)o3});
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(p.out) + orow + col) = uint2{w0, w1};
+    } else {
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.out) + orow + col) = float4{o0, o1, o2, o3};
     }
   }
   if constexpr (DUMP) {
-    if (slot >= 0 && h == 0) {
+    if (slot >= 0 && h == 0 && kg == 0) {
       p.row_m[slot] = GUARD ? 0 : (int)Mref;
       p.row_d[slot] = Dfin;
     }
     if constexpr (CAUSAL) {
       // blocks past the workgroup's last query are never visited: code 0, no exponent
-      if (slot >= 0) {
+      if (slot >= 0 && kg == 0) {
         for (int kb = 2 * nsteps + h; kb < N / 32; kb += 2) {
           *reinterpret_cast<POp*>(p.p_codes + (size_t)slot * (PV8 ? N : N / 2) + kb * (PV8 ? 32 : 16)) = POp{};
           p.block_exp[(size_t)slot * (N / 32) + kb] = (int16_t)-32768;
@@ -840,7 +1042,7 @@ fwd_mxfp4_kernel(const KParams p) {
       }
     }
   }
-  if (p.lse != nullptr && h == 0) {
+  if (p.lse != nullptr && h == 0 && kg == 0) {
     // ln(sum_j 2^y_ij) of the represented operator: 2^ref * D / 6, with ref = M_i
     // (online) or R_i + L (guard, whose published bytes are shifted down by L)
     constexpr float kLn2 = 0.69314718f, kLn6 = 1.79175947f;
@@ -848,7 +1050,7 @@ fwd_mxfp4_kernel(const KParams p) {
     // (FP8 route: D already carries the payload's 2^-7, and no 1/6)
     p.lse[(size_t)bh * N + qrow] = ref * kLn2 + (PV8 ? logf(Dfin) : logf(Dfin) - kLn6);
   }
-  if (p.wg_clock != nullptr && tid == 0) {
+  if (p.wg_clock != nullptr && tid == 0 && (int)blockIdx.x < p.n_clock) {
     // shader-clock cycles and 100 MHz constant-clock ticks this workgroup was resident
     const unsigned long long clk1 = __builtin_amdgcn_s_memtime(), rt1 = __builtin_amdgcn_s_memrealtime();
     p.wg_clock[2 * blockIdx.x] = clk1 - clk0;
@@ -856,27 +1058,33 @@ fwd_mxfp4_kernel(const KParams p) {
   }
 }
 
-template <int D, int NW, bool DUMP, int EX2, int VAR>
+template <int D, int QG, int KS, bool DUMP, int EX2, int VAR>
 hipError_t launch_directp(const KParams& kp, hipStream_t stream) {
-  hipLaunchKernelGGL((fwd_mxfp4_kernel<D, NW, DUMP, EX2, VAR>), dim3(kp.total), dim3(NW * 64), 0, stream, kp);
-  return hipGetLastError();
+  if constexpr (kHasShape<D, KS, VAR>) {
+    hipLaunchKernelGGL((fwd_mxfp4_kernel<D, QG, KS, DUMP, EX2, VAR>), dim3(kp.total), dim3(QG * KS * 64), 0, stream, kp);
+    return hipGetLastError();
+  } else {
+    return hipErrorInvalidValue;
+  }
 }
 
-// Every (D, NW, DUMP) variant of one EX2 density and reference variant.
-#define FP4ATTN_DIRECTP_VARIANTS(MACRO, EX2, VAR) \
-  MACRO(64, 4, false, EX2, VAR)                   \
-  MACRO(64, 4, true, EX2, VAR)                    \
-  MACRO(64, 8, false, EX2, VAR)                   \
-  MACRO(64, 8, true, EX2, VAR)                    \
-  MACRO(128, 4, false, EX2, VAR)                  \
-  MACRO(128, 4, true, EX2, VAR)                   \
-  MACRO(128, 8, false, EX2, VAR)                  \
-  MACRO(128, 8, true, EX2, VAR)
+// Every (D, QG, KS, DUMP) variant of one EX2 density and reference variant.
+#define FP4ATTN_DIRECTP_SHAPES(MACRO, D, DUMP, EX2, VAR) \
+  MACRO(D, 4, 1, DUMP, EX2, VAR)                         \
+  MACRO(D, 8, 1, DUMP, EX2, VAR)                         \
+  MACRO(D, 4, 2, DUMP, EX2, VAR)                         \
+  MACRO(D, 2, 4, DUMP, EX2, VAR)                         \
+  MACRO(D, 1, 8, DUMP, EX2, VAR)
+#define FP4ATTN_DIRECTP_VARIANTS(MACRO, EX2, VAR)      \
+  FP4ATTN_DIRECTP_SHAPES(MACRO, 64, false, EX2, VAR)   \
+  FP4ATTN_DIRECTP_SHAPES(MACRO, 64, true, EX2, VAR)    \
+  FP4ATTN_DIRECTP_SHAPES(MACRO, 128, false, EX2, VAR)  \
+  FP4ATTN_DIRECTP_SHAPES(MACRO, 128, true, EX2, VAR)
 
-#define FP4ATTN_DIRECTP_DECLARE(D, NW, DUMP, EX2, VAR) \
-  extern template hipError_t launch_directp<D, NW, DUMP, EX2, VAR>(const KParams&, hipStream_t);
-#define FP4ATTN_DIRECTP_DEFINE(D, NW, DUMP, EX2, VAR) \
-  template hipError_t launch_directp<D, NW, DUMP, EX2, VAR>(const KParams&, hipStream_t);
+#define FP4ATTN_DIRECTP_DECLARE(D, QG, KS, DUMP, EX2, VAR) \
+  extern template hipError_t launch_directp<D, QG, KS, DUMP, EX2, VAR>(const KParams&, hipStream_t);
+#define FP4ATTN_DIRECTP_DEFINE(D, QG, KS, DUMP, EX2, VAR) \
+  template hipError_t launch_directp<D, QG, KS, DUMP, EX2, VAR>(const KParams&, hipStream_t);
 
 }  // namespace directp_detail
 }  // namespace fp4attn

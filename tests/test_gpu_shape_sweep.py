@@ -57,6 +57,38 @@ def test_every_route_at_launch_boundaries(B, H, N, d):
     _run_fp8(fa, host64, dev, rows, label + " fp8")
 
 
+# Launches that split the keys of a workgroup's queries among its waves: 32, 64
+# and 128 queries per workgroup (eight, four and two key groups), tile counts that
+# leave key groups one stage short or without work, one to several turns of the ring.
+SPLIT_SHAPES = [
+    (1, 1, 512, 128),      # eight groups, one stage of four tiles
+    (1, 2, 640, 128),      # five tiles: one group of four has a tile in the second stage
+    (1, 2, 640, 64),       # four groups, three stages of two tiles, the last half filled
+    (1, 3, 1152, 64),      # eight groups, nine tiles
+    (1, 1, 4224, 128),     # eight groups, 33 tiles (causal: 32-query workgroups ending in every tile)
+    (3, 7, 640, 64),       # 105 workgroups of 128 queries: four groups
+    (1, 9, 2176, 128),     # two groups, 17 tiles (FP8 and causal too)
+    (2, 5, 1664, 64),      # two groups, 13 tiles
+    (1, 12, 2048, 64),     # 192 workgroups
+    (1, 5, 5120, 64),      # causal: four groups over 200 workgroups
+    (1, 3, 14080, 128),    # FP8 P/V over more queries than a round, no multiple of 256: two groups
+    (1, 20, 4096, 128),    # FP8 P/V, 320 wide workgroups: two groups instead
+]
+
+
+@pytest.mark.parametrize("B,H,N,d", SPLIT_SHAPES)
+def test_every_route_with_split_keys(B, H, N, d):
+    import paper_2609_04105_amd as fa
+    host64, dev, rows = _inputs(B, H, N, d)
+    label = f"split B{B} H{H} N{N} d{d}"
+    _run_and_check(fa, host64, dev, rows, label, lse=True)
+    _run_and_check(fa, host64, dev, rows, label + " causal", causal=True, lse=True)
+    _run_and_check(fa, host64, dev, rows, label + " ex2 16", ex2_pairs=16)
+    _run_guarded(fa, host64, dev, rows, label + " guard", 110, 16)
+    _run_fp8(fa, host64, dev, rows, label + " fp8")
+    _run_fp8(fa, host64, dev, rows, label + " fp8 causal", causal=True)
+
+
 @pytest.mark.parametrize("H,N,d", [(24, 32768, 128), (64, 32768, 64)])
 def test_paper_largest_shapes_sampled_rows(H, N, d):
     """The largest shapes of the paper's D128 and D64 tables (B1), in the launch the
