@@ -3,6 +3,10 @@
 Shapes follow include/fp4attn.h.  Inputs must be contiguous CUDA (HIP) tensors;
 outputs are allocated with torch unless passed in.  Work is enqueued on the
 current torch stream of the tensors' device.
+
+The calls of the attention path go through ``_binding`` (csrc/binding.cpp), which
+checks, allocates and launches natively and returns None for arguments that it does
+not take as they stand; those calls, and every error, go through the checks here.
 """
 import ctypes
 import math
@@ -10,6 +14,12 @@ import math
 import torch
 
 from ._lib import FP4ATTN_BF16, FP4ATTN_F32, ForwardOptions, check, lib
+
+try:
+    from . import _binding   # needs torch loaded
+except ImportError as e:
+    raise ImportError("the native call path _binding.so is missing or does not load: build it with "
+                      "`python paper_2609_04105_amd/build.py` (or __graft_entry__.build())") from e
 
 _DTYPES = {torch.float32: FP4ATTN_F32, torch.bfloat16: FP4ATTN_BF16}
 
@@ -32,6 +42,11 @@ def _same_device(*tensors):
         if t.device != dev:
             raise ValueError(f"tensors of one call must share a device: {dev} and {t.device}")
     return dev
+
+
+def _native(r):
+    """The result of a native call; raises its status."""
+    return check(r) if r.__class__ is int else r
 
 
 def _launch(device, fn, *args):
@@ -118,6 +133,9 @@ def quantize_qkv(q, k, v, anchored=False, pv_fp8=False):
     """Operands of the forward: MXFP4 Q, K along d; V along the sequence
     (transposed), MXFP4 or, with ``pv_fp8``, MXFP8.  ``anchored``: K and V in the
     anchor key order of the guarded forward (128 anchors)."""
+    r = _binding.quantize_qkv(q, k, v, anchored, pv_fp8)
+    if r is not None:
+        return _native(r)
     n_anchor = 128 if anchored else 0
     if _one_launch(q, k, v) and not (anchored and pv_fp8):
         lead, (rows, cols) = q.shape[:-2], q.shape[-2:]
@@ -193,6 +211,10 @@ def forward_mxfp4(q_codes, q_scales, k_codes, k_scales, vt_codes, vt_scales, sof
     normaliser) or ``pv_fp8`` (FP8 P and V; V from ``quantize_qkv(..., pv_fp8=True)``)
     select the extended entry point; otherwise the plain forward runs.
     """
+    r = _binding.forward(q_codes, q_scales, k_codes, k_scales, vt_codes, vt_scales, softmax_scale, affine_a, affine_b,
+                         out, out_dtype, ex2_pairs, guard, causal, lse, pv_fp8)
+    if r is not None:
+        return _native(r)
     B, H, N, d = _fp4_shape(q_codes)
     ops = (q_codes, q_scales, k_codes, k_scales, vt_codes, vt_scales)
     _check_operands(B, H, N, d, ops, pv_fp8)
@@ -217,6 +239,9 @@ def attention_mxfp4(q, k, v, softmax_scale=None, causal=False, lse=None, ex2_pai
     forward in one call: MXFP4 Q and K; V in MXFP4 or, with ``pv_fp8``, MXFP8; K and
     V in anchor order when ``guard`` is given.  The quantized operands are not kept
     (use :func:`quantize_qkv` and :func:`forward_mxfp4` to reuse them)."""
+    r = _binding.attention(q, k, v, softmax_scale, 1.5, 1.2, out, out_dtype, ex2_pairs, guard, causal, lse, pv_fp8)
+    if r is not None:
+        return _native(r)
     ops = quantize_qkv(q, k, v, anchored=guard is not None, pv_fp8=pv_fp8)
     return forward_mxfp4(*ops, softmax_scale=softmax_scale, out=out, out_dtype=out_dtype, ex2_pairs=ex2_pairs,
                          guard=guard, causal=causal, lse=lse, pv_fp8=pv_fp8)
@@ -278,6 +303,9 @@ def debug_mfma_stream(a_codes, b_codes, blocks, iters):
 
 def forward_bf16(q, k, v, softmax_scale=None, out=None, out_dtype=torch.float32):
     """Same-design BF16 attention forward; q, k, v [B, H, N, d] bf16."""
+    r = _binding.forward_bf16(q, k, v, softmax_scale, out, out_dtype)
+    if r is not None:
+        return _native(r)
     _need(q, "q", torch.bfloat16, 4)
     _need(k, "k", torch.bfloat16, 4)
     _need(v, "v", torch.bfloat16, 4)

@@ -1,12 +1,15 @@
-"""Build libfp4attn.so (the HIP kernels and the C-ABI) in-tree with hipcc for gfx950.
+"""Build libfp4attn.so (the HIP kernels and the C-ABI) in-tree with hipcc for gfx950,
+and _binding.so (the native call path of the Python binding) with the host compiler.
 
 Usage: python paper_2609_04105_amd/build.py [--jobs N]   (does not import the package)
 """
 import argparse
+import importlib.util
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -14,6 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libfp4attn.so")
+BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["fwd_mxfp4_guard.hip", "fwd_mxfp4_causal.hip", "fwd_mxfp4_ex2.hip", "fwd_mxfp4.hip",
            "fwd_mxfp4_ex2_dense.hip", "fwd_mxfp4_fp8pv.hip", "fwd_bf16.hip", "api.hip", "quantize.hip", "mfma_stream.hip"]
 # The attention kernels never rely on NaN ordering in fmax; without this flag the
@@ -48,19 +52,40 @@ def _compile(src):
     return obj
 
 
+def _run(what, cmd):
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{what} failed:\n{res.stderr}")
+
+
+def _build_binding():
+    """csrc/binding.cpp against the installed torch and the library just linked."""
+    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+    tmp = BINDING + ".tmp"
+    _run("binding build", [
+        os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM",
+        "-D__HIP_PLATFORM_AMD__", "-D_GLIBCXX_USE_CXX11_ABI=1", "-I" + sysconfig.get_paths()["include"],
+        "-isystem", os.path.join(torch_dir, "include"),
+        "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+        "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"),
+        os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L" + HERE, "-l:libfp4attn.so",
+        "-L" + os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+        "-Wl,-rpath,$ORIGIN"])
+    os.replace(tmp, BINDING)
+
+
 def build(jobs=8, verbose=True):
-    """Compile every HIP source for gfx950 and link the shared library (always rebuilds)."""
+    """Compile every HIP source for gfx950, link the shared library and build the
+    binding (always rebuilds)."""
     os.makedirs(BUILD, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp"
-    cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError(f"link failed:\n{res.stderr}")
+    _run("link", [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
+    _build_binding()
     if verbose:
-        print(f"built {LIB}")
+        print(f"built {LIB}\nbuilt {BINDING}")
     return LIB
 
 
