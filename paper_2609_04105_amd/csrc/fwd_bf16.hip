@@ -11,18 +11,19 @@
 //   the bf16 probabilities it computes are already its P^T operand of the PV
 //   product, with no cross-lane movement;
 // - K/V tiles of 64 keys in a four-stage LDS ring filled three tiles ahead by
-//   direct-to-LDS buffer loads: K in matrix-operand order, V in its natural
-//   [key][d] layout (16-byte chunks XOR-swizzled by key), read as the V^T
-//   operand by gfx950's transposing LDS read (ds_read_b64_tr_b16), so V is
-//   taken as [B, H, N, d] like Q and K;
+//   direct-to-LDS buffer loads, both in their natural [key][d] layout (16-byte
+//   chunks XOR-swizzled by key); V is read as the V^T operand by gfx950's
+//   transposing LDS read (ds_read_b64_tr_b16), so V is taken as [B, H, N, d] like
+//   Q and K;
 // - a two-deep software pipeline: while the vector ALU turns step g+1 into
 //   probabilities, the matrix unit runs PV of step g and QK of step g+2;
 // - an integer row reference with a lazy, exact power-of-two rescale (the
 //   reference may lag the row maximum by up to 32 binades), and the denominator
 //   from the same bf16 P operand on the matrix unit (an indicator-row
 //   16x16x32 product), so it sums exactly the probabilities PV consumes;
-// - the XCD-aware workgroup order of the MXFP4 forward, and its eight-wave
-//   workgroups at d = 128 (two per CU at four waves per SIMD at d = 64).
+// - the XCD-aware workgroup order of the MXFP4 forward, its eight-wave workgroups at
+//   d = 128 (two per CU at four waves per SIMD at d = 64), and its key split for
+//   grids that fill no whole round.
 #include "gfx950.hpp"
 #include "launch.hpp"
 
@@ -46,7 +47,7 @@ struct BParams {
 
 template <int D>
 struct BLayout {
-  static constexpr int kCodes = (kBN16 / 32) * (D / 16) * 1024;  // K fragments [step][d chunk][lane][16 B]
+  static constexpr int kCodes = kBN16 * D * 2;                   // K [key][d], swizzled 16-byte chunks
   static constexpr int vCodes = kBN16 * D * 2;                   // V [key][d], swizzled 16-byte chunks
   static constexpr int kOff = 0;
   static constexpr int vOff = kCodes;
@@ -73,12 +74,25 @@ __device__ __forceinline__ int key_of_row16(int m) {
   return 16 * (m >> 4) + 8 * ((m >> 2) & 1) + 4 * ((m >> 3) & 1) + (m & 3);
 }
 
+// K tiles in LDS: key r's 16-byte chunk c sits in slot c ^ k_swizzle16(r).  A copy's
+// lanes read whole rows (in operand order, another row per lane, the address unit
+// took them one at a time; no change in time here, where the copies were not the
+// bound), and an S^T operand read, which takes one chunk of
+// the 16 keys 16 q .. 16 q + 15 in each 16 lanes, meets all 16 bank groups.
+template <int D>
+__device__ __forceinline__ int k_swizzle16(int r) {
+  return D == 128 ? r & 15 : (r >> 1) & 7;
+}
+
 // Direct-to-LDS copy of lane l's 16 bytes at byte soff + off of `rsrc` to LDS
 // byte `lds` + 16 l (see the MXFP4 forward: not counted by the compiler, waited
-// for with vm_wait; bytes past the buffer's end read as zero).
+// for with vm_wait; bytes past the buffer's end read as zero; the offset goes
+// through a scalar move).
 __device__ __forceinline__ void lds_copy16_b(unsigned lds, __amdgpu_buffer_rsrc_t rsrc, int soff, unsigned off) {
-  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(off), "s"(rsrc),
-               "s"(__builtin_amdgcn_readfirstlane(soff)), "{m0}"(__builtin_amdgcn_readfirstlane(lds))
+  int so;
+  asm volatile("s_mov_b32 %0, %3\n\tbuffer_load_dwordx4 %1, %2, %0 offen lds"
+               : "=&s"(so)
+               : "v"(off), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff)), "{m0}"(__builtin_amdgcn_readfirstlane(lds))
                : "memory");
 }
 template <int n>
@@ -96,9 +110,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_buffer_b(const void* base
   return __builtin_amdgcn_make_buffer_rsrc(b, (short)0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
-// One 64-key tile: K fragments in operand order (item i = one lane's 16 bytes
-// of step s, d chunk c), then V rows in [key][d] order with the 16-byte chunk
-// c of key r stored at chunk slot c ^ v_swizzle(r).  Thread tid copies items
+// One 64-key tile: K rows, then V rows, in [key][d] order with the 16-byte chunk
+// c of key r stored at chunk slot c ^ k_swizzle16(r) or c ^ v_swizzle(r).  Thread tid copies items
 // tid, tid + NT, ...; the 64 lanes of a wave copy 64 consecutive items.
 template <int D, int NW>
 struct TileCopy16 {
@@ -126,9 +139,8 @@ struct TileCopy16 {
       buf[i] = is_k ? kbuf : vbuf;
       lds_off[i] = item0 * 16;
       if (is_k) {
-        const int m = item & 63, rest = item >> 6;
-        const int c = rest % (D / 16), s = rest / (D / 16);
-        off[i] = ((32 * s + key_of_row16(m & 31)) * D + 16 * c + 8 * (m >> 5)) * 2;
+        const int r = item / (D / 8), slot = item % (D / 8);
+        off[i] = (r * D + 8 * (slot ^ k_swizzle16<D>(r))) * 2;
       } else {
         const int p = item - nK, r = p / (D / 8), slot = p % (D / 8);
         off[i] = (r * D + 8 * (slot ^ v_swizzle<D>(r))) * 2;
@@ -143,6 +155,14 @@ struct TileCopy16 {
     for (int i = 0; i < kPerThread; ++i) lds_copy16_b(lds + lds_off[i], buf[i], key0 * D * 2, off[i]);
   }
 };
+
+// The accumulator is formed here and not moved below (emits nothing; device code
+// only, a 512-bit operand does not pass the host compiler's asm checks).
+__device__ __forceinline__ void pin_b(const v16f& a) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" ::"v"(a));
+#endif
+}
 
 __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
   typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
@@ -165,30 +185,23 @@ __device__ __forceinline__ uint2 lds_read_tr16(const uint8_t* p) {
 template <int D, int NW>
 constexpr int kMinWaves16 = (D == 128 && NW == 4) ? 1 : ((D == 64 && NW == 8) ? 4 : 2);
 
-template <int D, int NW, bool OUT_BF16>
+// KS = 2: two waves share a tile of 32 queries, each taking one 32-key step of every
+// key tile, and merge their sums at the end.
+template <int D, int NW, int KS, bool OUT_BF16>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(kMinWaves16<D, NW>, kMinWaves16<D, NW> > 2 ? 4 : 2))) void
 fwd_bf16_kernel(const BParams p) {
   using L = BLayout<D>;
-  constexpr int BM = NW * 32;
-  __shared__ __attribute__((aligned(16))) uint8_t ring0[L::stage];
-  __shared__ __attribute__((aligned(16))) uint8_t ring1[L::stage];
-  __shared__ __attribute__((aligned(16))) uint8_t ring2[L::stage];
-  __shared__ __attribute__((aligned(16))) uint8_t ring3[L::stage];
-  static_assert(kStages16 == 4, "one array per ring stage");
-  auto ring = [&](auto B_) -> uint8_t* {
-    constexpr int b = decltype(B_)::value % kStages16;
-    if constexpr (b == 0) return ring0;
-    else if constexpr (b == 1) return ring1;
-    else if constexpr (b == 2) return ring2;
-    else return ring3;
-  };
+  constexpr int QG = NW / KS, BM = QG * 32;
+  __shared__ __attribute__((aligned(16))) uint8_t ring_mem[kStages16 * L::stage];
+  auto ring = [&](auto B_) -> uint8_t* { return ring_mem + (decltype(B_)::value % kStages16) * L::stage; };
 
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, h = lane >> 5, lr = lane & 31;
   const int lin = xcd_remap(blockIdx.x, p.total);
   const int bh = lin / p.n_qtiles, qt = lin % p.n_qtiles;
   const int N = p.N;
-  const int qrow = qt * BM + wave * 32 + lr;
+  const int qg = KS == 1 ? wave : wave % QG, kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave) / QG;
+  const int qrow = qt * BM + qg * 32 + lr;
 
   const uint16_t* kp = p.k + (size_t)bh * N * D;
   const uint16_t* vp = p.v + (size_t)bh * N * D;
@@ -227,8 +240,15 @@ fwd_bf16_kernel(const BParams p) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int r = 8 * h + 4 * t + gi / 4;
-      v_lane[cc][t] = r * (2 * D) + 16 * ((4 * cc + 2 * gg + (gi & 3) / 2) ^ v_swizzle<D>(r)) + 8 * (gi & 1);
+      v_lane[cc][t] = kg * 32 * (2 * D) + r * (2 * D) + 16 * ((4 * cc + 2 * gg + (gi & 3) / 2) ^ v_swizzle<D>(r)) + 8 * (gi & 1);
     }
+
+  // Its chunk of K row key_of_row16(lr) for d chunk c is 2 c + h (the second step's
+  // rows are 32 keys on, which leaves the swizzle unchanged).
+  const int krow = key_of_row16(lr);
+  unsigned k_lane[D / 16];
+#pragma unroll
+  for (int c = 0; c < D / 16; ++c) k_lane[c] = L::kOff + (kg * 32 + krow) * (2 * D) + 16 * ((2 * c + h) ^ k_swizzle16<D>(krow));
 
   const int ntiles = N / kBN16;
   const int nsteps = 2 * ntiles;  // 32-key steps
@@ -239,7 +259,7 @@ fwd_bf16_kernel(const BParams p) {
     v16f a = v16f{};
     static_for<D / 16>([&](auto C_) {
       constexpr int c = decltype(C_)::value;
-      const v4i kf = *reinterpret_cast<const v4i*>(st + L::kOff + ((sl * (D / 16) + c) * 64 + lane) * 16);
+      const v4i kf = *reinterpret_cast<const v4i*>(st + k_lane[c] + sl * 32 * (2 * D));
       a = mfma_bf16_32x32x16(kf, qf[c], a);
     });
     acc = a;
@@ -335,79 +355,161 @@ fwd_bf16_kernel(const BParams p) {
   copy.issue(ring(I0{}), 0);
   copy.issue(ring(std::integral_constant<int, 1>{}), kBN16);
   copy.issue(ring(std::integral_constant<int, 2>{}), 2 * kBN16);
-  vm_wait_b<2 * kBatch>();  // tile 0 has landed
-  __syncthreads();
-
   v16f SA, SB;
   v4i PA[2], PB[2];
-  qk(ring(I0{}), std::integral_constant<int, 0>{}, SA);
-  softmax(SA, PA, std::false_type{});
-  qk(ring(I0{}), std::integral_constant<int, 1>{}, SA);
-
-  // One step of the pipeline (see the MXFP4 forward): PV of step g, the
-  // probabilities of step g+1, and QK of step g+2; j is the step's position in
-  // its group of eight, TAIL marks the tail group.
-  auto step = [&](auto J_, auto TAIL_, int g) {
-    constexpr int j = decltype(J_)::value;
-    constexpr bool tail = decltype(TAIL_)::value;
-    constexpr int sl = j % 2;
-    using b_cur = std::integral_constant<int, j / 2>;
-    using b_nxt = std::integral_constant<int, j / 2 + 1>;
-    using b_new = std::integral_constant<int, j / 2 + 3>;
-    auto& S_in = (sl == 0) ? SA : SB;   // S^T of step g+1
-    auto& S_out = (sl == 0) ? SB : SA;  // S^T of step g+2
-    auto& P_cur = (sl == 0) ? PA : PB;
-    auto& P_nxt = (sl == 0) ? PB : PA;
-    const int t = g >> 1;
-    pv(ring(b_cur{}), std::integral_constant<int, sl>{}, P_cur);
-    if (!tail || g + 1 < nsteps) softmax(S_in, P_nxt, std::bool_constant<!tail>{});
-    if constexpr (sl == 0) {
-      vm_wait_b<kBatch>();  // tile t+1 has landed: only tile t+2's loads may be in flight
+  if constexpr (KS == 2) {
+    // A wave has one step in each tile, so PV of tile t is done before the barrier
+    // that publishes tile t + 2, and that barrier frees tile t's stage.
+    copy.issue(ring(std::integral_constant<int, 3>{}), 3 * kBN16);
+    vm_wait_b<2 * kBatch>();  // tiles 0 and 1 have landed
+    __syncthreads();
+    qk(ring(I0{}), I0{}, SA);
+    softmax(SA, PA, std::false_type{});
+    qk(ring(std::integral_constant<int, 1>{}), I0{}, SB);
+    auto step = [&](auto J_, auto TAIL_, int t) {
+      constexpr int j = decltype(J_)::value;
+      constexpr bool tail = decltype(TAIL_)::value;
+      auto& S_in = (j % 2 == 0) ? SB : SA;   // S^T of tile t+1
+      auto& S_out = (j % 2 == 0) ? SA : SB;  // S^T of tile t+2
+      auto& P_cur = (j % 2 == 0) ? PA : PB;
+      auto& P_nxt = (j % 2 == 0) ? PB : PA;
+      pv(ring(std::integral_constant<int, j>{}), I0{}, P_cur);
+      if (!tail || t + 1 < ntiles) softmax(S_in, P_nxt, std::bool_constant<!tail>{});
+      vm_wait_b<kBatch>();  // tile t+2 has landed: only tile t+3's loads may be in flight
       __syncthreads();
-      copy.issue(ring(b_new{}), (t + 3) * kBN16);
-    }
-    if (!tail || g + 2 < nsteps) {
-      qk(ring(b_nxt{}), std::integral_constant<int, sl>{}, S_out);
-      asm volatile("" ::"v"(S_out));
-    }
-  };
+      copy.issue(ring(std::integral_constant<int, j>{}), (t + 4) * kBN16);
+      if (!tail || t + 2 < ntiles) {
+        qk(ring(std::integral_constant<int, j + 2>{}), I0{}, S_out);
+        pin_b(S_out);
+      }
+    };
+    int t0 = 0;
+    for (; t0 + 4 <= ntiles - 2; t0 += 4)
+      static_for<4>([&](auto J_) { step(J_, std::false_type{}, t0 + decltype(J_)::value); });
+    static_for<6>([&](auto J_) {
+      const int t = t0 + decltype(J_)::value;
+      if (t < ntiles) step(J_, std::true_type{}, t);
+    });
+  } else {
+    vm_wait_b<2 * kBatch>();  // tile 0 has landed
+    __syncthreads();
 
-  int g0 = 0;
-  for (; g0 + 8 <= nsteps - 2; g0 += 8) {
-    static_for<8>([&](auto J_) { step(J_, std::false_type{}, g0 + decltype(J_)::value); });
+    qk(ring(I0{}), std::integral_constant<int, 0>{}, SA);
+    softmax(SA, PA, std::false_type{});
+    qk(ring(I0{}), std::integral_constant<int, 1>{}, SA);
+
+    // One step of the pipeline (see the MXFP4 forward): PV of step g, the
+    // probabilities of step g+1, and QK of step g+2; j is the step's position in
+    // its group of eight, TAIL marks the tail group.
+    auto step = [&](auto J_, auto TAIL_, int g) {
+      constexpr int j = decltype(J_)::value;
+      constexpr bool tail = decltype(TAIL_)::value;
+      constexpr int sl = j % 2;
+      using b_cur = std::integral_constant<int, j / 2>;
+      using b_nxt = std::integral_constant<int, j / 2 + 1>;
+      using b_new = std::integral_constant<int, j / 2 + 3>;
+      auto& S_in = (sl == 0) ? SA : SB;   // S^T of step g+1
+      auto& S_out = (sl == 0) ? SB : SA;  // S^T of step g+2
+      auto& P_cur = (sl == 0) ? PA : PB;
+      auto& P_nxt = (sl == 0) ? PB : PA;
+      const int t = g >> 1;
+      pv(ring(b_cur{}), std::integral_constant<int, sl>{}, P_cur);
+      if (!tail || g + 1 < nsteps) softmax(S_in, P_nxt, std::bool_constant<!tail>{});
+      if constexpr (sl == 0) {
+        vm_wait_b<kBatch>();  // tile t+1 has landed: only tile t+2's loads may be in flight
+        __syncthreads();
+        copy.issue(ring(b_new{}), (t + 3) * kBN16);
+      }
+      if (!tail || g + 2 < nsteps) {
+        qk(ring(b_nxt{}), std::integral_constant<int, sl>{}, S_out);
+        asm volatile("" ::"v"(S_out));
+      }
+    };
+
+    int g0 = 0;
+    for (; g0 + 8 <= nsteps - 2; g0 += 8) {
+      static_for<8>([&](auto J_) { step(J_, std::false_type{}, g0 + decltype(J_)::value); });
+    }
+    static_for<10>([&](auto J_) {
+      const int g = g0 + decltype(J_)::value;
+      if (g < nsteps) step(J_, std::true_type{}, g);
+    });
   }
-  static_for<10>([&](auto J_) {
-    const int g = g0 + decltype(J_)::value;
-    if (g < nsteps) step(J_, std::true_type{}, g);
-  });
   vm_wait_b<0>();  // no copy may still be landing in LDS when the workgroup ends
 
   const float d_lo = lane_read(Dacc[0], lane & 15), d_hi = lane_read(Dacc[1], lane & 15);
-  const float inv = 1.0f / ((lane & 16) ? d_hi : d_lo);
+  float Dfin = (lane & 16) ? d_hi : d_lo;
+  // Quad q of the output: registers 4 (q % 4) .. + 3 of O[q / 4], columns
+  // 32 (q / 4) + 8 (q % 4) + 4 h .. + 3; after a key split each wave finishes half.
+  constexpr int kQuads = D / 8 / KS;
+  v4f own[kQuads];
+  auto quad = [&](auto Q_) {
+    constexpr int q = decltype(Q_)::value;
+    return v4f{O[q / 4][4 * (q % 4)], O[q / 4][4 * (q % 4) + 1], O[q / 4][4 * (q % 4) + 2], O[q / 4][4 * (q % 4) + 3]};
+  };
+  if constexpr (KS == 1) {
+    static_for<kQuads>([&](auto Q_) { own[decltype(Q_)::value] = quad(Q_); });
+  } else {
+    // Merge: both sums scaled to the larger reference by an exact power of two.
+    float* md = reinterpret_cast<float*>(ring_mem);                  // [kg][qg][M, D][32]
+    v4f* parts = reinterpret_cast<v4f*>(ring_mem + KS * QG * 256);  // [qg][finishing kg][quad][lane]
+    static_assert(KS * QG * 256 + QG * KS * kQuads * 1024 <= kStages16 * L::stage, "the merge fits the ring");
+    __syncthreads();  // every wave has read its last tile
+    if (h == 0) {
+      md[((kg * QG + qg) * 2) * 32 + lr] = Mref;
+      md[((kg * QG + qg) * 2 + 1) * 32 + lr] = Dfin;
+    }
+    __syncthreads();
+    const float Mo = md[(((1 - kg) * QG + qg) * 2) * 32 + lr], Do = md[(((1 - kg) * QG + qg) * 2 + 1) * 32 + lr];
+    const float M = fmaxf(Mref, Mo);
+    const int sh = (int)(Mref - M);
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) O[c][r] = ldexpf(O[c][r], sh);
+    Dfin = ldexpf(Dfin, sh) + ldexpf(Do, (int)(Mo - M));
+    static_for<KS>([&](auto F_) {  // F: the group that finishes these quads
+      constexpr int f = decltype(F_)::value;
+      if (kg == f) {
+        static_for<kQuads>([&](auto Q_) {
+          constexpr int q = decltype(Q_)::value;
+          own[q] = quad(std::integral_constant<int, f * kQuads + q>{});
+        });
+      } else {
+        v4f* dst = parts + (qg * KS + f) * (kQuads * 64) + lane;
+        static_for<kQuads>([&](auto Q_) {
+          constexpr int q = decltype(Q_)::value;
+          dst[q * 64] = quad(std::integral_constant<int, f * kQuads + q>{});
+        });
+      }
+    });
+    __syncthreads();
+    const v4f* src = parts + (qg * KS + kg) * (kQuads * 64) + lane;
+#pragma unroll
+    for (int q = 0; q < kQuads; ++q) own[q] += src[q * 64];
+  }
+  const float inv = 1.0f / Dfin;
   const size_t orow = ((size_t)bh * N + qrow) * D;
 #pragma unroll
-  for (int c = 0; c < D / 32; ++c) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col = 32 * c + 8 * g + 4 * h;
-      const float o0 = O[c][4 * g] * inv, o1 = O[c][4 * g + 1] * inv;
-      const float o2 = O[c][4 * g + 2] * inv, o3 = O[c][4 * g + 3] * inv;
-      if constexpr (OUT_BF16) {
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(p.out) + orow + col) =
-            uint2{pack_bf16(o0, o1), pack_bf16(o2, o3)};
-      } else {
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.out) + orow + col) = float4{o0, o1, o2, o3};
-      }
+  for (int i = 0; i < kQuads; ++i) {
+    const int q = kg * kQuads + i;
+    const int col = 32 * (q >> 2) + 8 * (q & 3) + 4 * h;
+    const float o0 = own[i][0] * inv, o1 = own[i][1] * inv, o2 = own[i][2] * inv, o3 = own[i][3] * inv;
+    if constexpr (OUT_BF16) {
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(p.out) + orow + col) =
+          uint2{pack_bf16(o0, o1), pack_bf16(o2, o3)};
+    } else {
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.out) + orow + col) = float4{o0, o1, o2, o3};
     }
   }
 }
 
-template <int D, int NW>
+template <int D, int NW, int KS = 1>
 hipError_t launch_b(const BParams& bp, bool out_bf16, hipStream_t stream) {
   if (out_bf16)
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, true>), dim3(bp.total), dim3(NW * 64), 0, stream, bp);
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, KS, true>), dim3(bp.total), dim3(NW * 64), 0, stream, bp);
   else
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, false>), dim3(bp.total), dim3(NW * 64), 0, stream, bp);
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, NW, KS, false>), dim3(bp.total), dim3(NW * 64), 0, stream, bp);
   return hipGetLastError();
 }
 
@@ -422,16 +524,35 @@ hipError_t launch_forward_bf16(const Bf16Args& a, hipStream_t stream) {
   bp.N = a.N;
   bp.sc = a.softmax_scale * kLog2Ef;
   const int bh = a.B * a.H;
-  // d = 128: eight-wave (256-query) workgroups when they fill the chip (four
-  // waves would run one wave per SIMD).  d = 64: eight-wave workgroups, two per
-  // CU, from half a round of them on.
-  const int64_t wide_wgs = a.N % 256 == 0 ? (int64_t)(a.N / 256) * bh : 0;
-  const bool wide = a.d == 128 ? wide_wgs >= 256 : wide_wgs >= 128;
+  // U workgroups of 128 queries, W of 256 (0 where N is no multiple of 256).  Wide: 256
+  // queries, eight waves; half: 128 queries, eight waves, the keys split in two;
+  // narrow: 128 queries, four waves (with d = 128 one wave per SIMD, since its ring
+  // fills the LDS).  Measured per launch (us, narrow / wide / half):
+  //   d 128 N 4096  U 128 81.0 / 102.4 / 60.7   U 384 161.6 / 110.8 / 128.6   U 640 242.3 / 228.0 / 199.3
+  //                 U 1024 333.2 / 260.1 / 282.2;  N 1024 U 768 79.6 / 70.9 / 72.2;  N 3968 U 744 239.6 / - / 202.7
+  //   d 64  N 4096  U 128 46.3 / 65.1 / 39.8    U 384 72.3 / 67.6 / 69.2      U 640 116.0 / 121.8 / 108.7
+  //                 U 896 149.3 / 134.0 / 144.2;  N 512 U 256 10.7 / 13.8 / 11.0, U 640 23.0 / 24.5 / 23.6
+  const int64_t U = (int64_t)bh * (a.N / 128), W = a.N % 256 == 0 ? U / 2 : 0;
+  bool wide, half;
+  if (a.d == 128) {
+    // half where its workgroups fit the CUs, where wide ones would leave a second
+    // round half empty, and wherever wide ones do not exist
+    half = a.N >= 512 && (U <= 256 || W == 0 || (W > 256 && W <= 384 && a.N >= 2048));
+    wide = !half && W > 128;
+  } else {
+    // likewise, two workgroups per CU
+    const bool second = U > 512 && U <= 768;
+    half = a.N >= 1024 && (U <= 256 || second || (W == 0 && U <= 768));
+    wide = !half && W > 128 && !second;
+  }
   const int BM = wide ? 256 : 128;
   bp.n_qtiles = a.N / BM;
   bp.total = bp.n_qtiles * bh;
-  if (a.d == 128) return wide ? launch_b<128, 8>(bp, a.out_bf16, stream) : launch_b<128, 4>(bp, a.out_bf16, stream);
-  return wide ? launch_b<64, 8>(bp, a.out_bf16, stream) : launch_b<64, 4>(bp, a.out_bf16, stream);
+  if (a.d == 128)
+    return half ? launch_b<128, 8, 2>(bp, a.out_bf16, stream)
+                : (wide ? launch_b<128, 8>(bp, a.out_bf16, stream) : launch_b<128, 4>(bp, a.out_bf16, stream));
+  return half ? launch_b<64, 8, 2>(bp, a.out_bf16, stream)
+              : (wide ? launch_b<64, 8>(bp, a.out_bf16, stream) : launch_b<64, 4>(bp, a.out_bf16, stream));
 }
 
 }  // namespace fp4attn

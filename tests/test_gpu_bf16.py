@@ -163,3 +163,20 @@ def test_bf16_launch_boundaries(fa, B, H, N, d):
     worst = float(row_rel_l2(got, ref).max())
     print(f"[bf16 sweep B{B} H{H} N{N} d{d}] rel-L2 {rel:.3e} cos {cos:.8f} worst row {worst:.3e}", flush=True)
     assert rel <= REL_MAX and cos >= COS_MIN and worst <= ROW_REL_MAX, (rel, cos, worst)
+
+
+@pytest.mark.parametrize("N,d,H", [(512, 128, 1), (640, 128, 2), (1152, 128, 1), (2176, 128, 2), (1024, 64, 1),
+                                   (1152, 64, 2), (1216 + 64, 64, 1)])
+def test_bf16_split_keys_all_rows(fa, N, d, H):
+    """Workgroups whose keys are split in two: 8 to 34 key tiles, whole and partial
+    turns of the ring of four, logits wide enough that the two halves' references
+    differ by many binades."""
+    g = torch.Generator().manual_seed(N + d)
+    q, k, v = (torch.randn(1, H, N, d, generator=g) for _ in range(3))
+    k[:, :, ::128] *= 40.0
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    host64 = tuple(workloads.as_f64(t) for t in (q, k, v))
+    dev = tuple(t.cuda() for t in (q, k, v))
+    _check(fa, host64, dev, np.arange(H * N), f"split N{N} d{d}")
+    out = fa.forward_bf16(*dev, out_dtype=torch.bfloat16)
+    assert torch.equal(out, fa.forward_bf16(*dev).to(torch.bfloat16))
