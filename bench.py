@@ -987,7 +987,7 @@ def main():
         "unit": "TFLOP/s",
         "frac": round(tflops / MXFP4_PEAK_TFLOPS, 4),
         "traffic": traffic,
-        "kernel": "fwd_mxfp4_kernel<128, 8, false, 0, 0>",
+        "kernel": "fwd_mxfp4_kernel<128, 8, 1, false, 0, 0>",
         "algorithmic_flops_per_launch": flops,
         "algorithmic_bytes_per_launch": int(w.B * w.H * (3 * w.N * w.d * (0.5 + 1 / 32) + 4 * w.N * w.d)),
         "counters": _counter_view(c_online, fp4_ms),

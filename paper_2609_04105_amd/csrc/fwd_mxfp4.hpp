@@ -40,9 +40,9 @@
 // - Denominator c_B: an extra 16x16x128 product of the same P^T register with a
 //   constant indicator operand, so it uses exactly the codes and E8M0 bytes of
 //   PV and costs no vector-ALU work.
-// - K/V tiles of 128 keys are staged in LDS in matrix-operand order (each
-//   lane's 16-byte fragment contiguous): a ring of four tiles filled three
-//   tiles ahead by direct-to-LDS loads.  The key loop is software
+// - K/V tiles of 128 keys are staged in LDS row by row (16-byte chunks swizzled,
+//   below): a ring of four tiles filled three tiles ahead by coalesced
+//   direct-to-LDS loads.  The key loop is software
 //   pipelined two deep: while the vector ALU maps step g+1 to codes, the
 //   matrix unit runs PV of step g and QK of step g+2.  With d = 64 and FP4 P/V
 //   the loop runs one step deep at four waves per SIMD instead.
