@@ -210,15 +210,18 @@ __device__ __forceinline__ unsigned mxfp8_block(const float (&v)[32], unsigned (
   return ubyte;
 }
 
-// The E8M0 bytes of blocks 8 grp .. 8 grp + 7 of one column (byte l of `run` is
-// block 8 grp + l) to `dst`: one 8-byte store when every column has whole groups
-// of 8 blocks (dst is then 8-byte aligned), else one byte per block that exists.
+// The E8M0 bytes of the NB (4 or 8) blocks of group `grp` of one column (byte l of
+// `run` is block NB grp + l) to `dst`: one store when every column has whole groups
+// (dst is then NB-byte aligned), else one byte per block that exists.
+template <int NB>
 __device__ __forceinline__ void store_scale_run(uint8_t* dst, uint2 run, int64_t nblk, int64_t grp) {
-  if (nblk % 8 == 0) {
-    *reinterpret_cast<uint2*>(dst) = run;
+  static_assert(NB == 4 || NB == 8, "one word or two");
+  if (nblk % NB == 0) {
+    if constexpr (NB == 8) *reinterpret_cast<uint2*>(dst) = run;
+    else *reinterpret_cast<unsigned*>(dst) = run.x;
   } else {
     const uint64_t bytes = ((uint64_t)run.y << 32) | run.x;
-    for (int l = 0; l < 8 && grp * 8 + l < nblk; ++l) dst[l] = (uint8_t)(bytes >> (8 * l));
+    for (int l = 0; l < NB && grp * NB + l < nblk; ++l) dst[l] = (uint8_t)(bytes >> (8 * l));
   }
 }
 
@@ -383,14 +386,13 @@ struct ColsJob {
   int64_t rows, cols, n_anchor, stride;
 };
 
-constexpr int kThreads = 512;     // one block of 32 values per thread
-constexpr int kColsPerWg = 64;    // V: columns x 8 blocks of 32 rows
-constexpr int kBlksPerWg = kThreads / kColsPerWg;
+constexpr int kThreads = 512;     // one block of 32 values per thread (the joint launch)
+constexpr int kColsPerWg = 64;    // V: 64 columns x one block of 32 rows per wave
 
 // Without the anchor order block t is at value 32 t: no division.
-template <typename T>
+template <typename T, int NT>
 __device__ __forceinline__ void quantize_rows(const RowsJob& j, unsigned wg) {
-  const int64_t t = (int64_t)wg * kThreads + threadIdx.x;
+  const int64_t t = (int64_t)wg * NT + threadIdx.x;
   if (t >= j.total) return;
   const T* src = static_cast<const T*>(j.src);
   int64_t at = t;
@@ -413,21 +415,22 @@ __device__ __forceinline__ void quantize_rows(const RowsJob& j, unsigned wg) {
   j.scales[t] = (uint8_t)u;
 }
 
-// Staged V^T: a workgroup takes 64 columns x 256 rows, wave w the block of 32 rows
-// w of them.  fp32: lane = column, 256-byte row segments.  bf16: lane l < 32 reads
+// Staged V^T: a workgroup of NT threads takes 64 columns x NT / 2 rows, wave w block w
+// of their 32-row blocks.  fp32: lane = column, 256-byte row segments.  bf16: lane l < 32 reads
 // rows 0-15 of the block at columns 2 l and 2 l + 1, lane l + 32 rows 16-31, and
 // one exchange of the wave's halves leaves column 2 l in lane l and column
 // 2 l + 1 in lane l + 32.  Codes and scale bytes are parked in LDS (chunks XOR'd
 // with the column, so that neither side meets bank conflicts) and leave as one
-// contiguous run per column (128 bytes, MXFP8 256) and one scale store.  The
+// contiguous run per column (128 bytes for 512 threads, MXFP8 256) and one scale store.  The
 // workgroups of the column groups of the same rows are launched next to each
 // other, so wider rows are read whole at about the same time.  cols % 64 == 0;
 // blocks past the last are skipped (their waves still meet the barrier).
-template <typename T, bool FP8>
+template <typename T, bool FP8, int NT>
 __device__ __forceinline__ void quantize_cols(const ColsJob& j, unsigned wg) {
+  constexpr int kBlksPerWg = NT / kColsPerWg;                 // blocks of 32 rows, one per wave
   constexpr int kChunks = FP8 ? 2 * kBlksPerWg : kBlksPerWg;  // 16-byte chunks of a column's run
   __shared__ uint4 code_lds[kColsPerWg][kChunks];
-  __shared__ uint2 scale_lds[kColsPerWg];
+  __shared__ uint2 scale_lds[kColsPerWg];  // 8 bytes a column, the first kBlksPerWg used
   const unsigned nblk = (unsigned)(j.rows / 32), ngrp = (nblk + kBlksPerWg - 1) / kBlksPerWg;
   const unsigned ncg = (unsigned)(j.cols / kColsPerWg);
   const unsigned rest = wg / ncg, cg = wg - rest * ncg, b = rest / ngrp, grp = rest - b * ngrp;
@@ -475,39 +478,39 @@ __device__ __forceinline__ void quantize_cols(const ColsJob& j, unsigned wg) {
     uint8_t* sb = reinterpret_cast<uint8_t*>(scale_lds);
     if constexpr (FP8) {
       unsigned w[8];
-      sb[kBlksPerWg * c + lb] = (uint8_t)bl.mxfp8(w);
-      code_lds[c][(2 * lb) ^ (c & 15)] = uint4{w[0], w[1], w[2], w[3]};
-      code_lds[c][(2 * lb + 1) ^ (c & 15)] = uint4{w[4], w[5], w[6], w[7]};
+      sb[8 * c + lb] = (uint8_t)bl.mxfp8(w);
+      code_lds[c][(2 * lb) ^ (c & (kChunks - 1))] = uint4{w[0], w[1], w[2], w[3]};
+      code_lds[c][(2 * lb + 1) ^ (c & (kChunks - 1))] = uint4{w[4], w[5], w[6], w[7]};
     } else {
       unsigned w[4];
-      sb[kBlksPerWg * c + lb] = (uint8_t)bl.mxfp4(w);
-      code_lds[c][lb ^ (c & 7)] = uint4{w[0], w[1], w[2], w[3]};
+      sb[8 * c + lb] = (uint8_t)bl.mxfp4(w);
+      code_lds[c][lb ^ (c & (kChunks - 1))] = uint4{w[0], w[1], w[2], w[3]};
     }
   }
   __syncthreads();
-  // eight lanes write a column's run, 128 contiguous bytes at a time
-  const int c = tid >> 3;
+  // kBlksPerWg lanes write a column's run, 16 bytes each at a time
+  const int c = tid / kBlksPerWg;
   const int64_t col = (int64_t)b * j.cols + cg * kColsPerWg + c;
   constexpr int kBlkChunks = FP8 ? 2 : 1;
   uint8_t* cdst = j.codes + (col * nblk + (int64_t)grp * kBlksPerWg) * (16 * kBlkChunks);
 #pragma unroll
   for (int k = 0; k < kBlkChunks; ++k) {
-    const int ch = (tid & 7) + 8 * k;
+    const int ch = tid % kBlksPerWg + kBlksPerWg * k;
     if (grp * kBlksPerWg + ch / kBlkChunks < nblk)
       *reinterpret_cast<uint4*>(cdst + ch * 16) = code_lds[c][ch ^ (c & (kChunks - 1))];
   }
   if (tid < kColsPerWg)
-    store_scale_run(j.scales + ((int64_t)b * j.cols + cg * kColsPerWg + tid) * nblk + grp * kBlksPerWg, scale_lds[tid],
+    store_scale_run<kBlksPerWg>(j.scales + ((int64_t)b * j.cols + cg * kColsPerWg + tid) * nblk + grp * kBlksPerWg, scale_lds[tid],
                     nblk, grp);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void quantize_mxfp4_rows_kernel(const RowsJob j) {
-  quantize_rows<T>(j, blockIdx.x);
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void quantize_mxfp4_rows_kernel(const RowsJob j) {
+  quantize_rows<T, NT>(j, blockIdx.x);
 }
-template <typename T, bool FP8>
-__global__ __launch_bounds__(kThreads) void quantize_cols_kernel(const ColsJob j) {
-  quantize_cols<T, FP8>(j, blockIdx.x);
+template <typename T, bool FP8, int NT>
+__global__ __launch_bounds__(NT) void quantize_cols_kernel(const ColsJob j) {
+  quantize_cols<T, FP8, NT>(j, blockIdx.x);
 }
 
 // Q, K and V in one launch: workgroups [0, n_v) take V (the longest of the three
@@ -519,9 +522,9 @@ template <typename T, bool FP8>
 __global__ __launch_bounds__(kThreads) void quantize_qkv_kernel(const RowsJob q, const RowsJob k, const ColsJob v,
                                                                 unsigned n_v, unsigned n_q) {
   const unsigned wg = blockIdx.x;
-  if (wg < n_v) quantize_cols<T, FP8>(v, wg);
-  else if (wg < n_v + n_q) quantize_rows<T>(q, wg - n_v);
-  else quantize_rows<T>(k, wg - n_v - n_q);
+  if (wg < n_v) quantize_cols<T, FP8, kThreads>(v, wg);
+  else if (wg < n_v + n_q) quantize_rows<T, kThreads>(q, wg - n_v);
+  else quantize_rows<T, kThreads>(k, wg - n_v - n_q);
 }
 
 // MXFP4, blocks along rows with transposed output, any number of columns: a
@@ -626,27 +629,41 @@ __global__ __launch_bounds__(256) void quantize_mxfp8_kernel(const T* __restrict
 
 namespace {
 
-int64_t workgroups(const RowsJob& j) { return (j.total + kThreads - 1) / kThreads; }
+template <int NT>
+int64_t workgroups(const RowsJob& j) { return (j.total + NT - 1) / NT; }
+template <int NT>
 int64_t workgroups(const ColsJob& j, int64_t batch) {
-  return batch * (j.cols / kColsPerWg) * ((j.rows / 32 + kBlksPerWg - 1) / kBlksPerWg);
+  constexpr int kBlks = NT / kColsPerWg;
+  return batch * (j.cols / kColsPerWg) * ((j.rows / 32 + kBlks - 1) / kBlks);
 }
 
-template <typename T>
-hipError_t launch_rows(const RowsJob& j, hipStream_t stream) {
-  hipLaunchKernelGGL((quantize_mxfp4_rows_kernel<T>), dim3((unsigned)workgroups(j)), dim3(kThreads), 0, stream, j);
+template <typename T, int NT>
+hipError_t launch_rows_nt(const RowsJob& j, hipStream_t stream) {
+  hipLaunchKernelGGL((quantize_mxfp4_rows_kernel<T, NT>), dim3((unsigned)workgroups<NT>(j)), dim3(NT), 0, stream, j);
   return hipGetLastError();
 }
 
-// A launch holds fewer than 2^32 threads; more matrices than that take several.
-constexpr int64_t kMaxWorkgroups = (int64_t(1) << 32) / kThreads - 1;
+// Rows in a launch of their own: 256 threads up to 327680 blocks, where workgroups of 512
+// leave the chip half filled or a round half empty (us, 256 / 512: bf16 1024 rows of 64
+// 2.94 / 3.46, 11 x 3968 rows of 128 4.41 / 5.00, 256 x 384 of 96 5.79 / 6.36; fp32 4.31 /
+// 5.02, 7.25 / 8.43); above, 512 is even (bf16 22 x 3968 of 128 6.51 / 6.57) or ahead (fp32
+// 11.7 / 11.1).
+template <typename T>
+hipError_t launch_rows(const RowsJob& j, hipStream_t stream) {
+  return j.total <= 5 << 16 ? launch_rows_nt<T, 256>(j, stream) : launch_rows_nt<T, kThreads>(j, stream);
+}
 
-template <typename T, bool FP8>
-hipError_t launch_cols(ColsJob j, int64_t batch, hipStream_t stream) {
-  const int64_t per = workgroups(j, 1), chunk = kMaxWorkgroups / per > 1 ? kMaxWorkgroups / per : 1;
+// A launch holds fewer than 2^32 threads; more matrices than that take several.
+template <int NT>
+constexpr int64_t kMaxWorkgroups = (int64_t(1) << 32) / NT - 1;
+
+template <typename T, bool FP8, int NT>
+hipError_t launch_cols_nt(ColsJob j, int64_t batch, hipStream_t stream) {
+  const int64_t per = workgroups<NT>(j, 1), fit = kMaxWorkgroups<NT> / per, chunk = fit > 1 ? fit : 1;
   const int64_t values = j.rows * j.cols;
   for (int64_t b = 0; b < batch; b += chunk) {
     const int64_t n = batch - b < chunk ? batch - b : chunk;
-    hipLaunchKernelGGL((quantize_cols_kernel<T, FP8>), dim3((unsigned)(n * per)), dim3(kThreads), 0, stream, j);
+    hipLaunchKernelGGL((quantize_cols_kernel<T, FP8, NT>), dim3((unsigned)(n * per)), dim3(NT), 0, stream, j);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     j.src = static_cast<const T*>(j.src) + n * values;
@@ -656,9 +673,21 @@ hipError_t launch_cols(ColsJob j, int64_t batch, hipStream_t stream) {
   return hipSuccess;
 }
 
+// V^T in a launch of its own: 256 threads up to 196608 blocks, where a grid of 512 leaves
+// the chip half filled or starts a round it does not fill (us, 256 / 512: 2 x 1024 rows of
+// 64, bf16 MXFP4 3.60 / 4.08, fp32 MXFP8 3.55 / 3.72; 11 x 3968 rows of 128 5.16 / 6.09,
+// 4.99 / 5.65), and for bf16 MXFP4 on every size (48 x 4096 rows of 128 14.5 / 16.1, 32 x
+// 16384 32.9 / 33.5).  The other types gain from the longer runs of 512 (24 x 4096 rows of
+// 128: fp32 MXFP4 13.7 / 12.35, MXFP8 11.25 / 10.6; 48 x 4096: bf16 MXFP8 14.6 / 13.9).
+template <typename T, bool FP8>
+hipError_t launch_cols(const ColsJob& j, int64_t batch, hipStream_t stream) {
+  const bool small = (sizeof(T) == 2 && !FP8) || batch * j.cols * (j.rows / 32) <= 3 << 16;
+  return small ? launch_cols_nt<T, FP8, 256>(j, batch, stream) : launch_cols_nt<T, FP8, kThreads>(j, batch, stream);
+}
+
 template <typename T, bool FP8>
 hipError_t launch_qkv(const RowsJob& q, const RowsJob& k, const ColsJob& v, int64_t batch, hipStream_t stream) {
-  const unsigned n_v = (unsigned)workgroups(v, batch), n_q = (unsigned)workgroups(q);
+  const unsigned n_v = (unsigned)workgroups<kThreads>(v, batch), n_q = (unsigned)workgroups<kThreads>(q);
   hipLaunchKernelGGL((quantize_qkv_kernel<T, FP8>), dim3(n_v + 2 * n_q), dim3(kThreads), 0, stream, q, k, v, n_v, n_q);
   return hipGetLastError();
 }
@@ -729,7 +758,7 @@ hipError_t launch_quantize_qkv(const QkvArgs& a, hipStream_t stream) {
   const RowsJob q{a.q, a.q_codes, a.q_scales, total, a.rows, a.cols / 32, 0, 0};
   const RowsJob k{a.k, a.k_codes, a.k_scales, total, a.rows, a.cols / 32, a.n_anchor, stride};
   const ColsJob v{a.v, a.vt_codes, a.vt_scales, a.rows, a.cols, a.n_anchor, stride};
-  if (a.cols % kColsPerWg != 0 || workgroups(v, a.batch) + 2 * workgroups(q) > kMaxWorkgroups) {
+  if (a.cols % kColsPerWg != 0 || workgroups<kThreads>(v, a.batch) + 2 * workgroups<kThreads>(q) > kMaxWorkgroups<kThreads>) {
     hipError_t e = launch_quantize_mxfp4(a.q, a.src_dtype, a.batch, a.rows, a.cols, 1, 0, a.q_codes, a.q_scales, stream);
     if (e != hipSuccess) return e;
     e = launch_quantize_mxfp4(a.k, a.src_dtype, a.batch, a.rows, a.cols, 1, a.n_anchor, a.k_codes, a.k_scales, stream);

@@ -35,7 +35,7 @@ def test_ragged_random(fa, dtype, axis):
 def test_staged_bf16_vt(fa, shape):
     """bf16 V^T with whole 64-column groups takes the staged kernel: ragged last
     groups of blocks (96 and 352 rows: 3 and 11 blocks per column, scale bytes
-    stored one by one) and whole ones (8-byte scale stores), one to three column
+    stored one by one) and whole ones (one store), one to three column
     groups, values over 40 binades."""
     g = torch.Generator().manual_seed(shape[1] + 3 * shape[2])
     x = (torch.randn(*shape, generator=g) * torch.exp2(torch.randint(-20, 20, shape, generator=g))).to(torch.bfloat16)
@@ -378,3 +378,24 @@ def test_qkv_in_one_launch(fa, dtype, anchored, pv_fp8, shape):
         assert all(torch.equal(a, b) for a, b in zip(got, want))
     with pytest.raises(ValueError):
         fa.quantize_qkv(q, k, v, anchored=True, pv_fp8=True)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("batch,rows,cols", [(48, 1056, 128),      # 202752 blocks: columns above the limit, rows below
+                                             (83, 992, 128)])      # 329344: both above
+def test_large_launches_equal_small_ones(fa, dtype, batch, rows, cols):
+    """Launches of their own change the workgroup size with the number of blocks
+    (columns at 196608, rows at 327680): the bytes of a large launch are those of its
+    matrices quantized a few at a time, partly filled last groups included (33 and 31
+    blocks per column)."""
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    x = torch.randn((batch, rows, cols), device="cuda", generator=g).to(dtype)
+    calls = [lambda t: fa.quantize_mxfp4(t, axis=-1), lambda t: fa.quantize_mxfp4(t, axis=-2),
+             lambda t: fa.quantize_mxfp4(t, axis=-1, n_anchor=rows // 32),
+             lambda t: fa.quantize_mxfp4(t, axis=-2, n_anchor=rows // 32), lambda t: fa.quantize_mxfp8(t, axis=-2)]
+    for i, call in enumerate(calls):
+        print(f"[large launch {i}] {batch}x{rows}x{cols} {dtype}", flush=True)
+        codes, scales = call(x)
+        for b in range(0, batch, 16):
+            c, s = call(x[b:b + 16])
+            assert torch.equal(codes[b:b + 16], c) and torch.equal(scales[b:b + 16], s), (i, b)
