@@ -26,6 +26,7 @@
 //   grids that fill no whole round.
 #include "gfx950.hpp"
 #include "launch.hpp"
+#include "launch_rules.hpp"
 
 namespace fp4attn {
 
@@ -518,6 +519,12 @@ hipError_t launch_b(const BParams& bp, bool out_bf16, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <int D>
+hipError_t dispatch_shape_b(const BParams& bp, Shape s, bool out_bf16, hipStream_t stream) {
+  if (s.ks == 2) return launch_b<D, 8, 2>(bp, out_bf16, stream);
+  return s.qg == 8 ? launch_b<D, 8>(bp, out_bf16, stream) : launch_b<D, 4>(bp, out_bf16, stream);
+}
+
 }  // namespace
 
 hipError_t launch_forward_bf16(const Bf16Args& a, hipStream_t stream) {
@@ -529,35 +536,10 @@ hipError_t launch_forward_bf16(const Bf16Args& a, hipStream_t stream) {
   bp.N = a.N;
   bp.sc = a.softmax_scale * kLog2Ef;
   const int bh = a.B * a.H;
-  // U workgroups of 128 queries, W of 256 (0 where N is no multiple of 256).  Wide: 256
-  // queries, eight waves; half: 128 queries, eight waves, the keys split in two;
-  // narrow: 128 queries, four waves (with d = 128 one wave per SIMD, since its ring
-  // fills the LDS).  Measured per launch (us, narrow / wide / half):
-  //   d 128 N 4096  U 128 81.0 / 102.4 / 60.7   U 384 161.6 / 110.8 / 128.6   U 640 242.3 / 228.0 / 199.3
-  //                 U 1024 333.2 / 260.1 / 282.2;  N 1024 U 768 79.6 / 70.9 / 72.2;  N 3968 U 744 239.6 / - / 202.7
-  //   d 64  N 4096  U 128 46.3 / 65.1 / 39.8    U 384 72.3 / 67.6 / 69.2      U 640 116.0 / 121.8 / 108.7
-  //                 U 896 149.3 / 134.0 / 144.2;  N 512 U 256 10.7 / 13.8 / 11.0, U 640 23.0 / 24.5 / 23.6
-  const int64_t U = (int64_t)bh * (a.N / 128), W = a.N % 256 == 0 ? U / 2 : 0;
-  bool wide, half;
-  if (a.d == 128) {
-    // half where its workgroups fit the CUs, where wide ones would leave a second
-    // round half empty, and wherever wide ones do not exist
-    half = a.N >= 512 && (U <= 256 || W == 0 || (W > 256 && W <= 384 && a.N >= 2048));
-    wide = !half && W > 128;
-  } else {
-    // likewise, two workgroups per CU
-    const bool second = U > 512 && U <= 768;
-    half = a.N >= 1024 && (U <= 256 || second || (W == 0 && U <= 768));
-    wide = !half && W > 128 && !second;
-  }
-  const int BM = wide ? 256 : 128;
-  bp.n_qtiles = a.N / BM;
+  const Shape shape = bf16_shape(a.d, a.N, bh);
+  bp.n_qtiles = a.N / (32 * shape.qg);
   bp.total = bp.n_qtiles * bh;
-  if (a.d == 128)
-    return half ? launch_b<128, 8, 2>(bp, a.out_bf16, stream)
-                : (wide ? launch_b<128, 8>(bp, a.out_bf16, stream) : launch_b<128, 4>(bp, a.out_bf16, stream));
-  return half ? launch_b<64, 8, 2>(bp, a.out_bf16, stream)
-              : (wide ? launch_b<64, 8>(bp, a.out_bf16, stream) : launch_b<64, 4>(bp, a.out_bf16, stream));
+  return a.d == 128 ? dispatch_shape_b<128>(bp, shape, a.out_bf16, stream) : dispatch_shape_b<64>(bp, shape, a.out_bf16, stream);
 }
 
 }  // namespace fp4attn

@@ -1,0 +1,52 @@
+"""The launch rules (csrc/launch_rules.hpp) on the CPU: compiled into a small host
+program and asked which workgroup shape a call takes."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+NAMES = {(4, 1): "narrow", (8, 1): "wide", (4, 2): "half", (2, 4): "quarter", (1, 8): "eighth"}
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ is not installed")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    """rules(lines) -> the shape's name per line of launch_rules.cpp's input."""
+    exe = tmp_path_factory.mktemp("rules") / "launch_rules"
+    res = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror",
+                          os.path.join(ROOT, "tests", "launch_rules.cpp"), "-o", str(exe)],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+
+    def ask(lines):
+        run = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, timeout=60)
+        assert run.returncode == 0
+        got = [NAMES[tuple(map(int, l.split()))] for l in run.stdout.splitlines()]
+        assert len(got) == len(lines)
+        return got
+    return ask
+
+
+def _line(d, N, bh, causal=False, fp8=False, bf16=False):
+    return f"b {d} {N} {bh}" if bf16 else f"f {d} {N} {bh} {int(causal)} {int(fp8)}"
+
+
+def _grid():
+    for d in (64, 128):
+        for N in (128, 256, 384, 512, 640, 768, 1024, 1152, 1664, 2048, 2176, 3968, 4096, 8192, 14080, 32768):
+            for bh in (*range(1, 70), 96, 128, 192, 257, 384, 512, 768, 1290, 3072, 6144):
+                yield d, N, bh
+
+
+def test_shapes_divide_the_rows(rules):
+    """Every launch covers N exactly: 256-query workgroups only where 256 divides N, and
+    no shape that does not exist (FP8 P/V at d = 128 has no eight-way split)."""
+    points = [(d, N, bh, dict(causal=c, fp8=f)) for d, N, bh in _grid() for c in (False, True) for f in (False, True)]
+    points += [(d, N, bh, dict(bf16=True)) for d, N, bh in _grid()]
+    for (d, N, bh, o), name in zip(points, rules([_line(d, N, bh, **o) for d, N, bh, o in points])):
+        assert name != "wide" or N % 256 == 0, (d, N, bh, o)
+        assert name != "eighth" or not (o.get("bf16") or (o.get("fp8") and d == 128)), (d, N, bh, o)
+        assert name != "quarter" or not o.get("bf16"), (d, N, bh, o)
