@@ -41,8 +41,12 @@ inline Shape directp_shape(int d, int N, int bh, bool causal, bool fp8) {
     // Whole rounds favour wide workgroups (N 4096 U 512 70.7 against 80.8 us); half takes
     // a second round that wide would leave half empty (U 640 114.8 / 132.5, U 768 120.3 /
     // 132.9), unequal workgroups (causal U 320 40.1 / 66.3, U 512 48.8 / 67.4), and every
-    // N that 256 does not divide (N 3968 U 744 110.9 against narrow's 148.0).
-    if (W == 0 || (causal ? U <= 512 : W > 256 && W <= 384)) return half;
+    // N that 256 does not divide (N 3968 U 744 110.9 against narrow's 148.0).  Not below
+    // N 1024 (half / wide: 44.8 / 46.1 there for U 544, but N 768 U 702 46.9 / 40.4, N 512
+    // U 768 35.8 / 32.1, N 256 U 768 29.5 / 25.6; causal N 256 U 512 19.4 / 16.5, N 512 U 512
+    // 21.9 / 19.4, U 384 18.6 / 18.6, U 288 15.8 / 17.6).
+    const bool split = causal ? U <= (N >= 1024 ? 512 : 384) : W > 256 && W <= 384 && N >= 1024;
+    if (W == 0 || split) return half;
     return W > 128 ? wide : narrow;
   }
   if (fp8) {

@@ -50,3 +50,21 @@ def test_shapes_divide_the_rows(rules):
         assert name != "wide" or N % 256 == 0, (d, N, bh, o)
         assert name != "eighth" or not (o.get("bf16") or (o.get("fp8") and d == 128)), (d, N, bh, o)
         assert name != "quarter" or not o.get("bf16"), (d, N, bh, o)
+
+
+def _check(rules, points):
+    """points: (d, N, workgroups of 128 queries, options, the shape measured fastest)"""
+    got = rules([_line(d, N, U * 128 // N, **o) for d, N, U, o, _ in points])
+    for (d, N, U, o, want), name in zip(points, got):
+        assert name == want, (d, N, U, o, name)
+
+
+def test_fp8_short_rows(rules):
+    """FP8 P/V at d = 128, rows under 1024: a second round is not worth a key split (it
+    took 8 to 17 % longer than the unsplit launch); long rows keep it."""
+    _check(rules, [(128, 256, 576, dict(fp8=True), "wide"), (128, 256, 768, dict(fp8=True), "wide"),
+                   (128, 512, 704, dict(fp8=True), "wide"), (128, 768, 702, dict(fp8=True), "wide"),
+                   (128, 1024, 704, dict(fp8=True), "half"), (128, 4096, 768, dict(fp8=True), "half"),
+                   (128, 256, 512, dict(fp8=True, causal=True), "wide"), (128, 512, 512, dict(fp8=True, causal=True), "wide"),
+                   (128, 512, 288, dict(fp8=True, causal=True), "half"), (128, 4096, 512, dict(fp8=True, causal=True), "half"),
+                   (128, 384, 513, dict(fp8=True), "half")])
