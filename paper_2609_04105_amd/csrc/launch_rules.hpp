@@ -27,7 +27,9 @@ struct Shape {
 // The causal forward's workgroups are half as long on average and unequal, so its
 // splits pay further: d 128 N 4096 U 192 31.8 / 42.9 / 27.8 / 24.1 / 34.4, U 512 38.2 / 44.8
 // / 36.6 / 52.2; d 64 N 2048 U 448 17.9 / 22.3 / 17.0 / 26.8; but N 1024 U 384 d 128 16.0 / 19.7
-// / 19.3.  FP8 P/V with d = 128 leaves one wave per SIMD to four-wave workgroups (LDS):
+// / 19.3, and below N 512 half never gains on narrow (narrow / half: d 128 N 128 U 8 6.5 / 7.1,
+// N 256 U 32 7.5 / 8.0; d 64 N 128 U 32 5.3 / 5.6, N 256 U 64 6.1 / 6.3).
+// FP8 P/V with d = 128 leaves one wave per SIMD to four-wave workgroups (LDS):
 // N 4096 U 128 52.6 / 65.9 / 38.8 / 26.3, U 256 54.5 / 67.0 / 42.8 / 48.0.
 inline Shape directp_shape(int d, int N, int bh, bool causal, bool fp8) {
   const int64_t U = (int64_t)bh * (N / 128), W = N % 256 == 0 ? U / 2 : 0;
@@ -52,13 +54,13 @@ inline Shape directp_shape(int d, int N, int bh, bool causal, bool fp8) {
   if (fp8) {
     // d = 64: narrow workgroups, two per CU, throughout (N 4096 U 768 81.1 against wide's
     // 106.6, U 4096 376 / 418).
-    return causal && U <= 512 && U <= N / 8 ? half : narrow;
+    return causal && N >= 512 && U <= 512 && U <= N / 8 ? half : narrow;
   }
   if (d == 64) {
     // Four waves per SIMD (one-step pipeline).  Wide workgroups, two per CU, for whole
     // half rounds (+4-8 % on large shapes; -6 to -15 % where the last is partly
     // filled) and, causal, from 3072 of them (+2.5-5.7 %; -1 to -2 % at 1024-2048).
-    if (causal ? U <= 640 && U <= N / 4 : U <= 512 && N >= 2048) return half;
+    if (causal ? N >= 512 && U <= 640 && U <= N / 4 : U <= 512 && N >= 2048) return half;
     return W >= (causal ? 3072 : 256) && W % 256 == 0 ? wide : narrow;
   }
   if (causal) {
@@ -66,7 +68,7 @@ inline Shape directp_shape(int d, int N, int bh, bool causal, bool fp8) {
     // U 4096 238 / 247; N 8192 U 1024 95.2 / 103.4), but not between two rounds and four
     // (N 4096 U 1280 78.4 / 71.9), and never for short rows (N 2048 U 512 28.4 / 23.4, U 4096
     // 175 / 172; N 1024 U 1024 33.3 / 30.7).
-    if (U <= 512 && U <= N / 8) return half;
+    if (N >= 512 && U <= 512 && U <= N / 8) return half;
     return N >= 4096 && ((W >= 384 && W <= 512) || W >= 1024) ? wide : narrow;
   }
   // Wide when more than half the CUs get one (N 4096 U 384 43.1 against 46.4, U 448 44.7 /

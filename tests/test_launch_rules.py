@@ -68,3 +68,13 @@ def test_fp8_short_rows(rules):
                    (128, 256, 512, dict(fp8=True, causal=True), "wide"), (128, 512, 512, dict(fp8=True, causal=True), "wide"),
                    (128, 512, 288, dict(fp8=True, causal=True), "half"), (128, 4096, 512, dict(fp8=True, causal=True), "half"),
                    (128, 384, 513, dict(fp8=True), "half")])
+
+
+def test_causal_short_rows(rules):
+    """Causal rows under 512 keys: the merge of a split costs more than the steps it saves
+    (it took 7 to 9 % longer at N 128); from 512 on few workgroups split."""
+    narrow = [(d, N, U, dict(causal=True, fp8=f), "narrow") for d, N, U, f in
+              ((128, 128, 2, False), (128, 128, 16, False), (128, 256, 32, False), (128, 384, 48, False),
+               (64, 128, 32, False), (64, 256, 64, False), (64, 384, 96, False), (64, 128, 16, True), (64, 256, 32, True))]
+    _check(rules, narrow + [(64, 1664, 416, dict(causal=True), "half"), (128, 4096, 512, dict(causal=True), "half"),
+                            (64, 4096, 512, dict(causal=True, fp8=True), "half")])
