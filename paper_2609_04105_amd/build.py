@@ -59,8 +59,15 @@ def _run(what, cmd):
 
 
 def _build_binding():
-    """csrc/binding.cpp against the installed torch and the library just linked."""
-    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+    """csrc/binding.cpp against the installed torch and the library just linked; False,
+    and no binding, where torch or its headers are not installed (the library and its
+    C-ABI need neither, and the package's calls then go through its Python checks)."""
+    spec = importlib.util.find_spec("torch")
+    torch_dir = spec.submodule_search_locations[0] if spec is not None else ""
+    if not os.path.exists(os.path.join(torch_dir, "include", "ATen", "core", "Tensor.h")):
+        if os.path.exists(BINDING):
+            os.remove(BINDING)   # of another torch and an older library
+        return False
     tmp = BINDING + ".tmp"
     _run("binding build", [
         os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM",
@@ -72,20 +79,21 @@ def _build_binding():
         "-L" + os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
         "-Wl,-rpath,$ORIGIN"])
     os.replace(tmp, BINDING)
+    return True
 
 
 def build(jobs=8, verbose=True):
-    """Compile every HIP source for gfx950, link the shared library and build the
-    binding (always rebuilds)."""
+    """Compile every HIP source for gfx950, link the shared library and, where torch is
+    installed, build the binding (always rebuilds)."""
     os.makedirs(BUILD, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp"
     _run("link", [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
-    _build_binding()
+    bound = _build_binding()
     if verbose:
-        print(f"built {LIB}\nbuilt {BINDING}")
+        print(f"built {LIB}\n" + (f"built {BINDING}" if bound else "torch or its headers are missing: no _binding.so"))
     return LIB
 
 
