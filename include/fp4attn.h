@@ -340,8 +340,9 @@ const char* fp4attn_status_string(int status);
 /* Detail of the last error returned on the calling thread ("" if none). */
 const char* fp4attn_last_error(void);
 
-/* ABI version of this header, (major << 16) | minor: 2.0 (fp4attn_forward_bf16
- * takes V as [B, H, N, d]; 1.x took V transposed). */
+/* ABI version of this header, (major << 16) | minor: 2.1 (2.1 adds
+ * fp4attn_quantize_qkv; 2.0: fp4attn_forward_bf16 takes V as [B, H, N, d], where
+ * 1.x took V transposed). */
 int fp4attn_abi_version(void);
 
 #ifdef __cplusplus

@@ -379,6 +379,6 @@ const char* fp4attn_status_string(int status) {
 
 const char* fp4attn_last_error(void) { return g_last_error; }
 
-int fp4attn_abi_version(void) { return (2 << 16) | 0; }
+int fp4attn_abi_version(void) { return (2 << 16) | 1; }
 
 }  // extern "C"

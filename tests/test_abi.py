@@ -46,6 +46,13 @@ def test_status_strings(lib):
     assert lib.fp4attn_abi_version() >> 16 == 2
 
 
+def test_version_tells_the_entry_points_apart(lib):
+    """A library that reports 2.1 has fp4attn_quantize_qkv (2.0 had not); the header
+    states the version that the library returns."""
+    assert lib.fp4attn_abi_version() == (2 << 16) | 1
+    assert re.search(r"ABI version of this header, \(major << 16\) \| minor: 2\.1 ", open(HEADER).read())
+
+
 FAKE = [ctypes.c_void_p(4096 * (i + 1)) for i in range(8)]   # aligned, never dereferenced
 
 
