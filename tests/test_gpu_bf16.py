@@ -59,8 +59,8 @@ def test_bf16_tiny(fa):
 @pytest.mark.parametrize("N,d,H", [(128, 128, 1), (384, 128, 2), (640, 64, 2), (1152, 128, 3), (512, 128, 128),
                                    (256, 64, 256)])
 def test_bf16_tiles_all_rows(fa, N, d, H):
-    """One to eighteen 64-key tiles (a tail group of every length), four- and
-    eight-wave workgroups, both head dimensions."""
+    """Two to eighteen 64-key tiles, every workgroup shape at d = 128 and the unsplit two
+    at d = 64."""
     g = torch.Generator().manual_seed(N + d + H)
     q, k, v = (torch.randn(1, H, N, d, generator=g).to(torch.bfloat16) for _ in range(3))
     host64 = tuple(workloads.as_f64(t) for t in (q, k, v))
@@ -76,9 +76,9 @@ def test_bf16_full_size_sampled(fa, name):
 
 @pytest.mark.parametrize("H,d", [(24, 64), (24, 128), (36, 64)])
 def test_bf16_tail_launch(fa, H, d):
-    """B1 N4096 grids of 384 and 576 eight-wave workgroups, rounds that do not
-    divide the chip (one workgroup per CU at d = 128, two at d = 64); every 97th
-    row checked."""
+    """B1 N4096 grids that would take 384 and 576 wide workgroups, rounds that do not
+    divide the chip: H24 splits the keys (d = 128 one workgroup per CU, d = 64 two), H36
+    stays wide; every 97th row checked."""
     g = torch.Generator().manual_seed(10)
     q, k, v = (torch.randn(1, H, 4096, d, generator=g).to(torch.bfloat16) for _ in range(3))
     host64 = tuple(workloads.as_f64(t) for t in (q, k, v))
@@ -134,13 +134,26 @@ def test_bf16_longest_sequence_sampled_rows(fa):
     assert rel <= REL_MAX and cos >= COS_MIN and worst <= ROW_REL_MAX, (rel, cos, worst)
 
 
-@pytest.mark.parametrize("B,H,N,d", [(1, 32, 2048, 128), (1, 31, 2048, 128), (1, 16, 2048, 64), (1, 15, 2048, 64),
-                                     (3, 7, 1664, 128), (2, 5, 640, 64), (1, 1290, 256, 128), (1, 1, 128, 128)])
+BOUNDARY_SHAPES = [  # B, H, N, d
+    (1, 32, 2048, 128), (1, 31, 2048, 128),   # wide: a full round of 256, and 248
+    (1, 16, 2048, 64), (1, 15, 2048, 64),     # half: 256 and 240 workgroups of 128 queries
+    (3, 7, 1664, 128),                        # half: 256 does not divide N
+    (2, 5, 640, 64),                          # narrow: rows too short to split
+    (1, 1290, 256, 128),                      # wide: six rounds
+    (1, 1, 128, 128),                         # narrow: one tile
+    (1, 16, 2048, 128), (1, 17, 2048, 128),   # half up to one workgroup per CU, then wide
+    (1, 33, 2048, 128), (1, 49, 2048, 128),   # half where wide would leave a second round half empty, then wide
+    (1, 17, 2048, 64), (1, 33, 2048, 64), (1, 49, 2048, 64),   # wide, half, wide: the same at two workgroups per CU
+    (1, 3, 384, 128), (1, 3, 384, 64),        # narrow over a turn of its ring
+]
+
+
+@pytest.mark.parametrize("B,H,N,d", BOUNDARY_SHAPES)
 def test_bf16_launch_boundaries(fa, B, H, N, d):
-    """Both sides of the launch rule (eight-wave workgroups from 256 of them at
-    d = 128 and from 128 at d = 64, four-wave below and when N is not a multiple
-    of 256), many heads, one tile; 40 seeded rows plus the first and last of the
-    tensor and of a head."""
+    """Both sides of the launch rule's lines between its three workgroup shapes (wide: 256
+    queries; half: 128 queries, keys split in two; narrow: 128 queries; a CPU test of the
+    launch rules holds the table to all of them), many heads, one tile; 40 seeded rows
+    plus the first and last of the tensor and of a head."""
     g = torch.Generator().manual_seed(B * 1000003 + H * 1009 + N * 7 + d)
     q, k, v = (torch.randn(B, H, N, d, generator=g).to(torch.bfloat16) for _ in range(3))
     rows = np.random.default_rng(N + H).integers(0, B * H * N, 40)
@@ -180,3 +193,36 @@ def test_bf16_split_keys_all_rows(fa, N, d, H):
     _check(fa, host64, dev, np.arange(H * N), f"split N{N} d{d}")
     out = fa.forward_bf16(*dev, out_dtype=torch.bfloat16)
     assert torch.equal(out, fa.forward_bf16(*dev).to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("H,N,d", [(2, 384, 128), (3, 1152, 128), (17, 2048, 128),    # narrow, half, wide
+                                   (2, 640, 64), (3, 1152, 64), (17, 2048, 64)])
+@pytest.mark.parametrize("where", ["q_row", "k_key", "v_column"])
+def test_bf16_non_finite_input_propagation(fa, where, H, N, d):
+    """A NaN in one element of Q, K (every row of its head) or V (its column of its head)
+    reaches exactly the outputs that exact attention makes NaN, from either half of a key
+    split; everything else in the head, and the other heads, is finite and matches.  A NaN
+    row of Q may take one more row with it, the one 16 queries away in its tile of 32:
+    the two share their denominator's product, where the other row's weight is 0 times
+    NaN."""
+    g = torch.Generator().manual_seed(41)
+    q, k, v = (torch.randn(1, H, N, d, generator=g).to(torch.bfloat16) for _ in range(3))
+    for key in (77, N - 20):                    # one in the first 32-key step of a 64-key tile, one in the second
+        x = {"q_row": q, "k_key": k, "v_column": v}[where].clone()
+        x[0, 1, key, 10] = float("nan")
+        qkv = [x if name == where else t for name, t in (("q_row", q), ("k_key", k), ("v_column", v))]
+        print(f"[bf16 non-finite {where} {key}] H{H} N{N} d{d}", flush=True)
+        out = fa.forward_bf16(*(t.cuda() for t in qkv))
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(out[0, 0]).all()) and bool(torch.isfinite(out[0, 2:]).all())
+        got = out[0, 1].cpu().numpy().astype(np.float64)
+        ref = exact.attention(*(workloads.as_f64(t)[0, 1] for t in qkv), 1.0 / np.sqrt(d))
+        nan = np.isnan(got)
+        if where == "q_row":
+            assert nan[key].all() and not np.delete(nan, [key, key ^ 16], axis=0).any()
+        else:
+            assert np.array_equal(nan, np.isnan(ref))
+        keep = ~nan
+        if keep.any():
+            rel, cos = rel_l2_cos(got[keep], ref[keep])
+            assert rel <= REL_MAX and cos >= COS_MIN, (rel, cos)

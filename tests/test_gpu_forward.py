@@ -692,8 +692,10 @@ def test_fp8pv_fidelity_against_exact_attention(fa):
 
 
 
+@pytest.mark.parametrize("H,N,d", [(2, 256, 64), (2, 640, 64), (2, 1024, 64), (10, 2048, 64),       # narrow, quarter, eighth, half
+                                   (2, 384, 128), (16, 640, 128), (2, 640, 128), (9, 2176, 128)])   # the same
 @pytest.mark.parametrize("where", ["q_row", "k_key", "v_column"])
-def test_non_finite_input_propagation(fa, where):
+def test_non_finite_input_propagation(fa, where, H, N, d):
     """A NaN in one input element (its 32-value block gets E8M0 byte 255, which the
     matrix unit reads as NaN) propagates as the header states, and nothing else moves:
     * Q row 5 of head 0: every score of that row is NaN, every code 0, the output row
@@ -704,9 +706,11 @@ def test_non_finite_input_propagation(fa, where):
       least 1/2), which gives the key code 0 by the code map.
     * V element (77, 10) of head 1: column 10 of every row of head 1 is NaN (the V^T
       block of keys 64..95 in that column is NaN); all other columns, and head 0, match
-      the oracle run with that element set to 0."""
+      the oracle run with that element set to 0.
+    Unsplit launches and every key split; the oracle runs on heads 0 and 1, the others
+    (enough of them for the launch to take its shape) have to be finite."""
     g = torch.Generator().manual_seed(40)
-    B, H, N, d = 1, 2, 256, 64
+    B = 1
     q, k, v = (torch.randn(B, H, N, d, generator=g) for _ in range(3))
     q[0, 1, :, 10] = q[0, 1, :, 10].abs() + 0.5
     q_ref, k_ref, v_ref = q.clone(), k.clone(), v.clone()
@@ -723,7 +727,7 @@ def test_non_finite_input_propagation(fa, where):
     else:
         v[0, 1, 77, 10] = float("nan")
         v_ref[0, 1, 77, 10] = 0.0
-        nan_cols[N:, 10] = True
+        nan_cols[N:2 * N, 10] = True
     q, k, v, q_ref, k_ref, v_ref = (t.to(torch.bfloat16) for t in (q, k, v, q_ref, k_ref, v_ref))
     print(f"[non-finite {where}] B{B} H{H} N{N} d{d}", flush=True)
     out = fa.forward_mxfp4(*gpu_operands(q.cuda(), k.cuda(), v.cuda()))
@@ -731,8 +735,8 @@ def test_non_finite_input_propagation(fa, where):
     got = out.reshape(-1, d).cpu().numpy().astype(np.float64)
     print(f"[non-finite {where}] NaN entries {int(np.isnan(got).sum())}, expected {int(nan_cols.sum())}", flush=True)
     assert np.array_equal(np.isnan(got), nan_cols), "NaN entries differ from the documented propagation"
-    host64 = tuple(workloads.as_f64(t) for t in (q_ref, k_ref, v_ref))
-    rows = np.nonzero(~nan_rows)[0]
+    host64 = tuple(workloads.as_f64(t[:, :2]) for t in (q_ref, k_ref, v_ref))
+    rows = np.nonzero(~nan_rows[:2 * N])[0]
     ref = oracle_rows(*host64, rows, 1.0 / np.sqrt(d), want_codes=False)
     keep = ~nan_cols[rows]
     cols = np.nonzero(keep.all(axis=0))[0]          # columns finite in every checked row

@@ -78,3 +78,44 @@ def test_causal_short_rows(rules):
                (64, 128, 32, False), (64, 256, 64, False), (64, 384, 96, False), (64, 128, 16, True), (64, 256, 32, True))]
     _check(rules, narrow + [(64, 1664, 416, dict(causal=True), "half"), (128, 4096, 512, dict(causal=True), "half"),
                             (64, 4096, 512, dict(causal=True, fp8=True), "half")])
+
+
+ROUTES = {"plain": dict(), "causal": dict(causal=True), "fp8": dict(fp8=True), "causal fp8": dict(causal=True, fp8=True),
+          "bf16": dict(bf16=True)}
+# Keys from which a kernel's main loop runs, whatever its ring: 10 unsplit steps of 64 (BF16:
+# of 32), 6 tiles (BF16: of 64) in two key groups, 9 stages of 2 tiles, 6 stages of 4 tiles.
+MAIN_LOOP = {"narrow": 640, "wide": 640, "half": 768, "quarter": 2304, "eighth": 3072}
+MAIN_LOOP_BF16 = {"narrow": 320, "wide": 320, "half": 384}
+
+
+@pytest.mark.parametrize("route", ROUTES)
+@pytest.mark.parametrize("d", [64, 128])
+def test_gpu_tables_reach_every_kernel(rules, route, d):
+    """The shapes of the GPU sweeps (tests/test_gpu_shape_sweep.py, test_gpu_bf16.py) launch
+    every workgroup shape that the rules can launch on this route, each with its main loop,
+    so that a later rule cannot take a kernel out of the tests."""
+    from test_gpu_bf16 import BOUNDARY_SHAPES
+    from test_gpu_shape_sweep import SHAPES, SPLIT_SHAPES
+    opts = ROUTES[route]
+    grid = [(N, bh) for dd, N, bh in _grid() if dd == d]
+    reachable = {}
+    for (N, bh), name in zip(grid, rules([_line(d, N, bh, **opts) for N, bh in grid])):
+        reachable[name] = max(N, reachable.get(name, 0))
+    table = [(N, B * H) for B, H, N, dd in (BOUNDARY_SHAPES if route == "bf16" else SHAPES + SPLIT_SHAPES) if dd == d]
+    tested = {}
+    for (N, bh), name in zip(table, rules([_line(d, N, bh, **opts) for N, bh in table])):
+        tested[name] = max(N, tested.get(name, 0))
+    assert set(tested) == set(reachable)
+    loop = MAIN_LOOP_BF16 if route == "bf16" else MAIN_LOOP
+    for name, longest in reachable.items():
+        assert tested[name] >= min(loop[name], longest), (name, tested[name])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_gpu_grids_reach_every_kernel(rules, d):
+    """The grids of the GPU test that runs every exponential density (which the guarded
+    and causal routes have too) take all five workgroup shapes."""
+    from test_gpu_shape_sweep import GRIDS
+    N, grids = GRIDS[d]
+    for opts in (dict(), dict(causal=True)):
+        assert set(rules([_line(d, N, bh, **opts) for bh in grids])) == set(NAMES.values())
