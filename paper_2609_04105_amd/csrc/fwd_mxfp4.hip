@@ -5,7 +5,6 @@
 // fwd_mxfp4_causal.hip, the FP8 P/V route from fwd_mxfp4_fp8pv.hip, all
 // compiled in parallel with this file.
 #include "fwd_mxfp4.hpp"
-#include "launch_rules.hpp"
 
 namespace fp4attn {
 namespace directp_detail {

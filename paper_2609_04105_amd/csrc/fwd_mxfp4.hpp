@@ -58,6 +58,7 @@
 
 #include "gfx950.hpp"
 #include "launch.hpp"
+#include "launch_rules.hpp"
 
 namespace fp4attn {
 namespace directp_detail {
@@ -330,14 +331,11 @@ constexpr int kTilesPerStage = KS > 2 ? KS / 2 : 1;
 constexpr int kLdsBytes = 160 * 1024;
 template <int D, int KS, int VAR>
 constexpr int kFit = kLdsBytes / (kTilesPerStage<KS> * Layout<D, (VAR & kPV8) != 0>::stage);
-template <int D, int QG, int KS, int VAR>
-constexpr int kRing = kFit<D, KS, VAR> < kStages ? kFit<D, KS, VAR> : kStages;
-// Shapes that exist: at least two stages must fit (not FP8 V with d = 128 and KS = 8).
 template <int D, int KS, int VAR>
-constexpr bool kHasShape = (kFit<D, KS, VAR>) >= 2;
+constexpr int kRing = kFit<D, KS, VAR> < kStages ? kFit<D, KS, VAR> : kStages;
 // One step deep: d = 64 (above), and where the ring holds two stages only.
-template <int D, int QG, int KS, int VAR>
-constexpr bool kOneDeep = kOneBuffer<D, VAR> || kRing<D, QG, KS, VAR> == 2;
+template <int D, int KS, int VAR>
+constexpr bool kOneDeep = kOneBuffer<D, VAR> || kRing<D, KS, VAR> == 2;
 // Two waves per SIMD, except where the LDS ring allows one workgroup of four
 // waves per CU only (FP8 V tiles with d = 128: 108 KiB), and four for the
 // one-buffer form above.
@@ -360,7 +358,8 @@ fwd_mxfp4_kernel(const KParams p) {
   using L = Layout<D, (VAR & kPV8) != 0>;
   constexpr int BM = QG * 32;
   // The LDS ring; the merge of a key split reuses it.
-  constexpr int TPS = kTilesPerStage<KS>, NST = kRing<D, QG, KS, VAR>;
+  constexpr int TPS = kTilesPerStage<KS>, NST = kRing<D, KS, VAR>;
+  static_assert(NST >= 2, "a stage is read while the next one is filled");
   __shared__ __attribute__((aligned(16))) uint8_t ring_mem[NST * TPS * L::stage];
   auto ring = [&](auto B_) -> uint8_t* { return ring_mem + (decltype(B_)::value % NST) * (TPS * L::stage); };
   using I0 = std::integral_constant<int, 0>;
@@ -709,7 +708,7 @@ fwd_mxfp4_kernel(const KParams p) {
     // Key split.  A wave has one step in each stage, so PV of stage t is done
     // before the barrier that publishes the next stage it reads, and that barrier
     // frees stage t: the ring is refilled one whole turn ahead.
-    constexpr bool ONE = kOneDeep<D, QG, KS, VAR>;
+    constexpr bool ONE = kOneDeep<D, KS, VAR>;
     constexpr int AHEAD = ONE ? 1 : 2;            // stage t publishes stage t + AHEAD
     constexpr int kFly = (NST - 1 - AHEAD) * kBatch;  // copies that may be in flight then
     const int nst = (ntiles + TPS - 1) / TPS;     // stages
@@ -1068,7 +1067,7 @@ fwd_mxfp4_kernel(const KParams p) {
 
 template <int D, int QG, int KS, bool DUMP, int EX2, int VAR>
 hipError_t launch_directp(const KParams& kp, hipStream_t stream) {
-  if constexpr (kHasShape<D, KS, VAR>) {
+  if constexpr (directp_launches(D, (VAR & 7) == kVarCausal, (VAR & kPV8) != 0, Shape{QG, KS})) {
     hipLaunchKernelGGL((fwd_mxfp4_kernel<D, QG, KS, DUMP, EX2, VAR>), dim3(kp.total), dim3(QG * KS * 64), 0, stream, kp);
     return hipGetLastError();
   } else {

@@ -79,6 +79,14 @@ inline Shape directp_shape(int d, int N, int bh, bool causal, bool fp8) {
   return W > (N >= 1024 ? 128 : 255) && !tail ? wide : narrow;
 }
 
+// Whether directp_shape ever returns `s`: a kernel is built for these only.  FP8 P/V with
+// d = 64 takes no wide workgroups; with d = 128 its eighth does not fit the LDS, and its
+// causal form splits every grid that wide workgroups do not fill.
+constexpr bool directp_launches(int d, bool causal, bool fp8, Shape s) {
+  const bool wide = s.qg == 8, narrow = s.qg == 4 && s.ks == 1;
+  return !fp8 || (d == 64 ? !wide : s.ks != 8 && !(causal && narrow));
+}
+
 // The same for the BF16 forward (U and W as above).  Wide: 256
 // queries, eight waves; half: 128 queries, eight waves, the keys split in two;
 // narrow: 128 queries, four waves (with d = 128 one wave per SIMD, since its ring

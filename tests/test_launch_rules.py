@@ -14,7 +14,7 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ is not 
 
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
-    """rules(lines) -> the shape's name per line of launch_rules.cpp's input."""
+    """rules(lines) -> the shape's name (k lines: a bool) per line of launch_rules.cpp's input."""
     exe = tmp_path_factory.mktemp("rules") / "launch_rules"
     res = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror",
                           os.path.join(ROOT, "tests", "launch_rules.cpp"), "-o", str(exe)],
@@ -24,7 +24,7 @@ def rules(tmp_path_factory):
     def ask(lines):
         run = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, timeout=60)
         assert run.returncode == 0
-        got = [NAMES[tuple(map(int, l.split()))] for l in run.stdout.splitlines()]
+        got = [NAMES[tuple(map(int, l.split()))] if " " in l else l == "1" for l in run.stdout.splitlines()]
         assert len(got) == len(lines)
         return got
     return ask
@@ -50,6 +50,16 @@ def test_shapes_divide_the_rows(rules):
         assert name != "wide" or N % 256 == 0, (d, N, bh, o)
         assert name != "eighth" or not (o.get("bf16") or (o.get("fp8") and d == 128)), (d, N, bh, o)
         assert name != "quarter" or not o.get("bf16"), (d, N, bh, o)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_kernels_built_are_the_kernels_launched(rules, d, causal, fp8):
+    """A kernel is built for exactly the shapes that the rule returns for some grid."""
+    launched = set(rules([_line(dd, N, bh, causal, fp8) for dd, N, bh in _grid() if dd == d]))
+    built = rules([f"k {d} {int(causal)} {int(fp8)} {qg} {ks}" for qg, ks in NAMES])
+    assert launched == {name for name, b in zip(NAMES.values(), built) if b}
 
 
 def _check(rules, points):
