@@ -8,13 +8,13 @@
 //   O_i   = sum_B 2^(E_B - M_i) sum_j q_ij (6 Vhat_j) / (6 sum_B 2^(E_B - M_i) c_B)
 //
 // gfx950 design
-// - One workgroup = NW waves = 32 * NW query rows of one (batch, head); each
-//   wave owns 32 queries for the whole key loop.  Both products run on the
-//   scaled FP4 matrix unit (v_mfma_scale_f32_32x32x64_f8f6f4) in transposed
-//   form: S^T = K Q^T and O^T = V^T P^T.  Lane l then holds query l % 32 in
-//   every accumulator, so the per-row online state (integer reference M_i, the
-//   lazy power-of-two rescale) is a per-lane scalar and needs no cross-lane
-//   broadcast.
+// - One workgroup = QG * KS waves = 32 * QG query rows of one (batch, head); a
+//   wave owns 32 queries, for the whole key loop (KS = 1) or for one of KS key
+//   groups (the key split below).  Both products run on the scaled FP4 matrix
+//   unit (v_mfma_scale_f32_32x32x64_f8f6f4) in transposed form: S^T = K Q^T and
+//   O^T = V^T P^T.  Lane l then holds query l % 32 in every accumulator, so the
+//   per-row online state (integer reference M_i, the lazy power-of-two rescale)
+//   is a per-lane scalar and needs no cross-lane broadcast.
 // - Keys are fed to the S^T product in a permuted order (key_of_row below)
 //   so that, with the 32x32 accumulator layout, lane half h holds all 32
 //   scores of N32 block h of each 64-key step, in key order, in the registers
@@ -45,7 +45,8 @@
 //   direct-to-LDS loads.  The key loop is software
 //   pipelined two deep: while the vector ALU maps step g+1 to codes, the
 //   matrix unit runs PV of step g and QK of step g+2.  With d = 64 and FP4 P/V
-//   the loop runs one step deep at four waves per SIMD instead.
+//   the loop runs one step deep instead, at four waves per SIMD (two with four or
+//   eight key groups).
 // - Small grids split the keys of a query tile among 2, 4 or 8 waves of the
 //   workgroup, each taking one 64-key step in turn, and merge their sums in LDS:
 //   codes do not depend on the reference and the merge scales by exact powers of
@@ -322,7 +323,8 @@ struct TileCopy {
 // query tiles and QG * KS waves.
 //
 // The FP4 P/V routes with d = 64 pipeline the key loop one step deep (one S^T
-// buffer, one P operand) to fit 128 registers: four waves per SIMD.
+// buffer, one P operand) to fit 128 registers: four waves per SIMD (a split into four or
+// eight takes more LDS and runs two).
 template <int D, int VAR>
 constexpr bool kOneBuffer = D == 64 && (VAR & kPV8) == 0;
 // Key tiles per LDS stage, and stages in the ring.
@@ -584,7 +586,7 @@ fwd_mxfp4_kernel(const KParams p) {
           *reinterpret_cast<v8i*>(p.p_codes + (size_t)slot * N + (2 * g + h) * 32) = keyorder;
         }
       }
-      // Operand k order (see TileCopy::issue): the lower half keeps keys 0-15 of
+      // Operand k order (see v_lane): the lower half keeps keys 0-15 of
       // block 0 and takes keys 0-15 of block 1; the upper half takes keys 16-31
       // of block 0 and keeps keys 16-31 of block 1.
 #pragma unroll

@@ -31,6 +31,14 @@ struct Shape {
 // N 256 U 32 7.5 / 8.0; d 64 N 128 U 32 5.3 / 5.6, N 256 U 64 6.1 / 6.3).
 // FP8 P/V with d = 128 leaves one wave per SIMD to four-wave workgroups (LDS):
 // N 4096 U 128 52.6 / 65.9 / 38.8 / 26.3, U 256 54.5 / 67.0 / 42.8 / 48.0.
+// The guarded and exponential routes share the plain lines: (110, 16) and 16 of 16 pairs,
+// d 128 N 4096 U 32 31.0 / 41.6 / 25.6 / 17.9 / 15.5 and 37.2 / 56.4 / 32.7 / 21.7 / 16.8, U 128
+// 32.2 / 42.7 / 27.7 / 21.5 / 32.6 and 38.9 / 57.9 / 35.3 / 25.6 / 35.5, U 256 34.8 / 44.0 / 30.9 /
+// 39.0 / 60.0 and 41.0 / 58.8 / 37.5 / 45.9 / 64.7, U 384 48.9 / 44.7 / 54.8 and 61.9 / 59.6 / 68.4, U 768
+// 79.2 / 89.3 / 83.7 and 93.1 / 114.8 / 102.4; d 64 N 4096 U 512 38.8 / 38.4 / 36.1 and 52.9 / 52.3 /
+// 49.0.  Over 183 grids of N 512 to 8192 the rule's shape takes 0.2 % (guard), 0.4 % (4 pairs) and
+// 0.6 % (16) longer than the fastest on geometric mean; the most, 8 to 11 %, at N 512 and
+// U 1024 to 3072, where narrow is ahead of wide on the plain route too.
 inline Shape directp_shape(int d, int N, int bh, bool causal, bool fp8) {
   const int64_t U = (int64_t)bh * (N / 128), W = N % 256 == 0 ? U / 2 : 0;
   const Shape narrow{4, 1}, wide{8, 1}, half{4, 2}, quarter{2, 4}, eighth{1, 8};
@@ -64,9 +72,10 @@ inline Shape directp_shape(int d, int N, int bh, bool causal, bool fp8) {
     return W >= (causal ? 3072 : 256) && W % 256 == 0 ? wide : narrow;
   }
   if (causal) {
-    // Wide from a round and a half on for long rows (N 4096 U 1024 57.0 against 58.9,
-    // U 4096 238 / 247; N 8192 U 1024 95.2 / 103.4), but not between two rounds and four
-    // (N 4096 U 1280 78.4 / 71.9), and never for short rows (N 2048 U 512 28.4 / 23.4, U 4096
+    // Wide from a round and a half on for long rows (N 4096 U 768 47.8 against 49.6, U 896
+    // 55.0 / 56.3, U 1024 57.0 / 58.9, U 4096 238 / 247; N 8192 U 768 82.5 / 82.9, U 896 89.4 / 98.0,
+    // U 1024 95.2 / 103.4), but not below (N 4096 U 640 45.9 / 41.1), nor between two rounds
+    // and four (N 4096 U 1280 78.4 / 71.9, U 1536 90.0 / 84.9; N 8192 U 1280 132.1 / 127.7), and never for short rows (N 2048 U 512 28.4 / 23.4, U 4096
     // 175 / 172; N 1024 U 1024 33.3 / 30.7).
     if (N >= 512 && U <= 512 && U <= N / 8) return half;
     return N >= 4096 && ((W >= 384 && W <= 512) || W >= 1024) ? wide : narrow;
@@ -92,7 +101,7 @@ constexpr bool directp_launches(int d, bool causal, bool fp8, Shape s) {
 // narrow: 128 queries, four waves (with d = 128 one wave per SIMD, since its ring
 // fills the LDS).  Measured per launch (us, narrow / wide / half):
 //   d 128 N 4096  U 128 81.0 / 102.4 / 60.7   U 384 161.6 / 110.8 / 128.6   U 640 242.3 / 228.0 / 199.3
-//                 U 1024 333.2 / 260.1 / 282.2;  N 1024 U 768 79.6 / 70.9 / 72.2;  N 3968 U 744 239.6 / - / 202.7
+//                 U 768 234.0 / 218.6 / 201.1   U 896 307.3 / 225.6 / 252.8   U 1024 333.2 / 260.1 / 282.2;  N 1024 U 768 79.6 / 70.9 / 72.2;  N 3968 U 744 239.6 / - / 202.7
 //   d 64  N 4096  U 128 46.3 / 65.1 / 39.8    U 384 72.3 / 67.6 / 69.2      U 640 116.0 / 121.8 / 108.7
 //                 U 896 149.3 / 134.0 / 144.2;  N 512 U 256 10.7 / 13.8 / 11.0, U 640 23.0 / 24.5 / 23.6
 inline Shape bf16_shape(int d, int N, int bh) {
