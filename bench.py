@@ -46,8 +46,9 @@ EX2_SWEEP = (1, 2, 4, 16)
 GUARD_ML = (110, 16)
 COUNTER_FILE = os.path.join(ROOT, "profiles", "counters_routes.json")
 CSRC = os.path.join(ROOT, "paper_2609_04105_amd", "csrc")
-KERNEL_SOURCES = [os.path.join(CSRC, f) for f in ("fwd_mxfp4.hpp", "fwd_mxfp4.hip", "gfx950.hpp", "launch.hpp")]
-BF16_SOURCES = [os.path.join(CSRC, f) for f in ("fwd_bf16.hip", "gfx950.hpp", "launch.hpp")]
+KERNEL_SOURCES = [os.path.join(CSRC, f) for f in ("fwd_mxfp4.hpp", "fwd_mxfp4.hip", "gfx950.hpp", "launch.hpp",
+                                                          "launch_rules.hpp")]
+BF16_SOURCES = [os.path.join(CSRC, f) for f in ("fwd_bf16.hip", "gfx950.hpp", "launch.hpp", "launch_rules.hpp")]
 
 
 def _source_sha(paths=None):

@@ -105,3 +105,14 @@ def test_source_hash_ignores_comments(bench, tmp_path):
     assert bench._source_sha([str(a)]) == bench._source_sha([str(b)])
     b.write_text("int x = 2;\nint y;\n")
     assert bench._source_sha([str(a)]) != bench._source_sha([str(b)])
+
+
+def test_source_hash_covers_every_included_header(bench):
+    """A change of any header that the kernels include (the launch rules among them)
+    detaches the committed counters."""
+    for sources in (bench.KERNEL_SOURCES, bench.BF16_SOURCES):
+        names = {os.path.basename(p) for p in sources}
+        for path in sources:
+            with open(path) as f:
+                included = {line.split('"')[1] for line in f if line.startswith('#include "')}
+            assert included <= names, (path, included - names)
