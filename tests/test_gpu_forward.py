@@ -63,7 +63,8 @@ def test_small_all_rows(fa):
 
 @pytest.mark.parametrize("N,d", [(384, 128), (640, 64), (1152, 128)])
 def test_ragged_tiles_all_rows(fa, N, d):
-    """Several key tiles and a query-tile count that does not fill whole 8-wave groups."""
+    """Three, five and nine key tiles: an unsplit launch, and four and eight key groups that
+    do not all have a last step."""
     g = torch.Generator().manual_seed(N + d)
     q, k, v = (torch.randn(1, 2, N, d, generator=g).to(torch.bfloat16) for _ in range(3))
     host64 = tuple(workloads.as_f64(t) for t in (q, k, v))
@@ -567,7 +568,8 @@ def test_causal_small_all_rows(fa, ex2_pairs):
 
 @pytest.mark.parametrize("N,d,H", [(128, 64, 1), (384, 128, 2), (1152, 128, 2), (512, 128, 128)])
 def test_causal_tiles_all_rows(fa, N, d, H):
-    """One key tile, 4-wave workgroups with a partial last group, and the 8-wave launch."""
+    """One and three key tiles unsplit, nine in eight key groups (a workgroup's last tile
+    partly masked), and an unsplit launch over two workgroups per CU."""
     g = torch.Generator().manual_seed(N + d + H)
     q, k, v = (torch.randn(1, H, N, d, generator=g).to(torch.bfloat16) for _ in range(3))
     host64 = tuple(workloads.as_f64(t) for t in (q, k, v))
